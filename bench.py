@@ -67,23 +67,10 @@ NN_FLOPS_PER_SITE = {"nn_conv0": 9 * 5 * 64 * 2, "nn_conv": 9 * 64 * 64 * 2}
 # WRITE x1.0); the summaries with their commands are under profiles/.  An
 # entry holds only while the sources its kernels are built from hash to
 # `source_sha256`; otherwise the bench reports null.
-_PROP_FILES = ("fft.hpp", "kernels.hpp")
-_NN_FILES = ("kernels.hpp", "nn.hpp")
 MEASURED_TRAFFIC = {
-    # profiles/prop_cfg3_traffic.md: the tuned propagator passes on 1024 x 512, N = 64
-    ("cfg3", "prop_row"): dict(bytes_per_launch=16168805, files=_PROP_FILES,
-                               source_sha256="877088b805e92cfbe6994e99c9fc2c678ef2c3253a7fbadb1721b17fee5559c1"),
-    ("cfg3", "prop_col"): dict(bytes_per_launch=17296672, files=_PROP_FILES,
-                               source_sha256="877088b805e92cfbe6994e99c9fc2c678ef2c3253a7fbadb1721b17fee5559c1"),
-    # profiles/nn_conv_cfg5q_traffic.md: mean over the two 64 -> 64 launches of a surrogate step
-    ("cfg5q", "nn_conv"): dict(bytes_per_launch=63871133, files=_NN_FILES,
-                               source_sha256="d085c160fd00ceae2554be7dfed9b4249a4a78738a1216f4bc593522dcf7a606"),
     # profiles/lb3_fluid3d_256_traffic.md: the step kernel without moment stores
     ("fluid3d_256", "lb3"): dict(bytes_per_launch=2873793431, files=("lb3.hpp",),
                                  source_sha256="e7e59f031e128b313dda272b0a26b0ab5c5fe413ad9252a506d9b009c091450e"),
-    # profiles/epd3_densities_256_traffic.md: mean over the five FFT passes of a contour step
-    ("densities3d_256_N32", "p3_fft"): dict(bytes_per_launch=295385359, files=("epd3.hpp",),
-                                            source_sha256="0f8cbbb975abf58193e39b668c073a1b5acfb5f18cfb18bb1665b18b037520b1"),
 }
 
 

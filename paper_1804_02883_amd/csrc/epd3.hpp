@@ -2,250 +2,286 @@
 // (Sec. II: the split step, the density integrals and Eq. phi_s, with the
 // heat kernel exp(-R_G^2 |k|^2 ds) of three dimensions).
 //
-// One contour step q -> E K (E q), E = exp(-(w_j - c_j)/2), runs as
-//   FFT along x of E q (the factor applied as the lines load) -> FFT along y
-//   -> FFT along z, heat multiplier, inverse FFT along z -> inverse FFT along
-//   y -> inverse FFT along x, storing q' = E Re / n.
-// The FFT kernel transforms whole lines in LDS with the radix-2 Stockham
-// formulation (natural order in and out, a ping-pong pair of buffers per
-// line): every line is read and written once per pass.  Lines along x are
-// contiguous; lines along y and z are strided, and a block's lines are
-// neighbours in x, so each load instruction of a wave covers consecutive
-// addresses.  Sums (gauge, Q_P, Q_S) are FP64 block partials in fixed slots,
-// added in slot order.
+// The heat kernel separates, K = K_x K_y K_z, and the factors commute, so a
+// contour step q -> E K (E q), E = exp(-(w_j - c_j)/2), is three real
+// one-dimensional convolutions, in the order x, y, z on even steps and z, y, x
+// on odd ones.  The last convolution of step a and the first of step a + 1
+// then run along the same axis and share a pass: convolve, multiply by E_a,
+// store q_{a+1}, multiply by E_{a+1}, convolve.  Two real lines ride in one
+// complex transform (the multiplier is real and even), both chains in one
+// launch (blockIdx.y), and the planes between the passes stay real: a contour
+// step moves 6 planes per chain (the shared pass: scratch and factor in, q and
+// scratch out; the y pass: scratch in and out).
+//
+// What bounds it: HBM at large sizes (launch latency below about 64^3, where a
+// pass is 6-7 us).  As one three-dimensional complex transform pair per step, a
+// chain at a time, a step moved 22 planes per chain in 5 launches.  Measured at
+// 256^3 FP32, N = 32: 320 launches of 120 us, 39.4 ms per evaluation, before;
+// 65 launches of 106 us (403 MB each, 3.8 TB/s; a copy reaches 5.05), 7.9 ms,
+// now.  128^3: 4.99 -> 1.12 ms (FP32), 9.32 -> 1.77 ms (FP64).
+//
+// The sums (gauge, Q_P, Q_S) are FP64 block partials in fixed slots, added in
+// slot order.
 #pragma once
-#include <hip/hip_runtime.h>
+#include "kernels.hpp"
 
 namespace epdlb {
 namespace epd3 {
 
 constexpr int kThreads = 256;
-constexpr int kRedBlocks = 256;
+constexpr int kRedBlocks = 1024;
 constexpr int kMaxLen = 512;
 
-template <typename T> struct Cx {
-  T re, im;
-};
-
-__device__ __forceinline__ void sin_cos_pi(double x, double* s, double* c) { sincospi(x, s, c); }
-__device__ __forceinline__ void sin_cos_pi(float x, float* s, float* c) { sincospif(x, s, c); }
-
-// c = exp(-(a (wA - cA) + (1 - a)(wB - cB)) / 2), the gauge from the field sums.
-template <typename T>
-__device__ __forceinline__ T half_step_factor(T wa, T wb, T a, const double* sums, double inv_n) {
-  const T cA = T(sums[0] * inv_n), cB = T(sums[2] * inv_n);
-  return exp(-(a * (wa - cA) + (T(1) - a) * (wb - cB)) * T(0.5));
-}
-
-struct LineArgs {
-  int L;         // line length (power of two, <= kMaxLen)
-  long st;       // element stride along the line
-  long count;    // number of lines
-  long g;        // base(l) = (l / g) * gs + (l % g) * gi
-  long gs, gi;
-  int mode;      // -1 forward, +1 inverse, 2 forward, heat multiplier, inverse
-  int lb;        // lines per block; > 0: lines interleaved across lanes (strided passes)
-  int nx, ny, nz;
-  double heat;   // R_G^2 ds (2 pi / dx)^2: |k|^2 R_G^2 ds = heat (mx^2/nx^2 + my^2/ny^2 + mz^2/nz^2)
-  // x passes only: fuse = 1 loads E q (q == nullptr: E) instead of C; fuse = 2
-  // stores q' = E Re(.) / n instead of C (E from wA, wB, a and the field sums)
-  int fuse;
-  const void* wA;
-  const void* wB;
-  const void* q;
-  void* qn;
-  const double* sums;
+// One pass of the propagators: lines of length L along one axis.
+template <typename T> struct PassArgs {
+  const T* wA;
+  const T* wB;
+  T* EA;                // exp(-(w_A - c_A)/2), written by the first pass
+  T* EB;
+  const double* sums;   // field sums: [0] w_A, [1] w_B
   double inv_n;
-  double a;
+  T* q[2];              // mid: the plane q_{a+1} of each chain
+  T* tmp;               // 2 planes (per chain): data between two passes
+  const T2<T>* tw;      // the twiddles of TwTables<T, L, R>
+  const T* mult;        // exp(-R_G^2 k^2 ds)/L in FFT order: L values, then what their rounding left
+  long n;               // sites, the plane stride
+  long units;           // pairs of lines
+  long rows;            // contiguous lines: their number (the last pair may be half empty)
+  long inner, gs, st;   // strided lines: pair u starts at (u / inner) gs + 2 (u % inner), element stride st
+  int first;            // input is E(step 0) (q_0 = 1) instead of tmp; writes EA and EB
+  int conv;             // convolve (0: the first pass of a grid with one axis, which only forms E)
+  int mid;              // after the convolution: x E(step a), store q_{a+1}
+  int second;           // then x E(step a + 1) and convolve again (2: no convolution, one axis)
+  int last;             // with mid: partial sums of q_N
+  T frac[2][2];         // A fraction of the segment of chain c at step a (+0/+1)
+  double* partials;     // last: per-block sums of q_N of the forward chain
 };
 
-// Stockham transform of the lines held in LDS (natural order in and out):
-// one radix-2 stage when log2 L is odd, then radix-4 stages; src and dst
-// alternate, *out receives the buffer that holds the result.  dir -1 or +1.
-// tw[m] = (cos, sin)(pi m / (L/2)), m < L: the stage of sub-length Ns takes
-// the angle dir pi r k / (2 Ns) (radix 4, r < 4) from entry r k L / (4 Ns),
-// and dir pi k / Ns (radix 2) from entry k L / (2 Ns).
-template <typename T>
-__device__ __forceinline__ void stockham(Cx<T>* buf0, Cx<T>* buf1, const Cx<T>* tw, int L, int t, int TL,
-                                         bool active, int dir, Cx<T>** out) {
-  Cx<T>* src = buf0;
-  Cx<T>* dst = buf1;
-  int Ns = 1;
-  if (L > 1 && (__builtin_ctz(unsigned(L)) & 1)) {
-    if (active) {
-      for (int j = t; j < L / 2; j += TL) {
-        const int k = j % Ns;
-        const Cx<T> w = tw[k * (L / (2 * Ns))];
-        const T c = w.re, s = dir > 0 ? w.im : -w.im;
-        const Cx<T> u = src[j];
-        const Cx<T> v0 = src[j + L / 2];
-        const T vr = v0.re * c - v0.im * s, vi = v0.re * s + v0.im * c;
-        const int d = (j / Ns) * Ns * 2 + k;
-        dst[d].re = u.re + vr;
-        dst[d].im = u.im + vi;
-        dst[d + Ns].re = u.re - vr;
-        dst[d + Ns].im = u.im - vi;
-      }
-    }
-    __syncthreads();
-    Cx<T>* tmp = src;
-    src = dst;
-    dst = tmp;
-    Ns = 2;
-  }
-  for (; Ns < L; Ns *= 4) {
-    if (active) {
-      for (int j = t; j < L / 4; j += TL) {
-        const int k = j % Ns;
-        const int step = k * (L / (4 * Ns));
-        T vr[4], vi[4];
+// Transforms per block of a pass over strided lines: 256 or 512 lanes, and
+// neighbouring lanes on neighbouring pairs: 128-byte segments (a whole cache
+// line) for lengths up to 256 in FP32 and 512 in FP64 (64 bytes at 512 in FP32,
+// where 16 pairs would need 1,024 lanes).
+template <typename T, int L, int R> constexpr int strided_nf() {
+  constexpr int tl = L / R;
+  constexpr int wide = sizeof(T) == 4 ? 16 : 8;   // pairs of one 128-byte segment
+  return tl * wide <= 256 ? 256 / tl : (tl * wide <= 512 ? wide : 512 / tl);
+}
+// Values per lane: whole short lines, else 8.
+template <int L> constexpr int values_per_lane() { return L < 8 ? L : 8; }
+
+// Convolution with the multiplier g + gl.  Every contour step applies the same
+// operator, so an error of the rounded multiplier, or of a twiddle, adds up
+// over the steps coherently, as rounding errors of the data do not.  Measured
+// at 256^3 FP32, N = 32, relative error of Phi_A: 5.7e-7 with rounded
+// multipliers and twiddles from two preloaded ones by products, 3.4e-7 with
+// both as here (3.8-4.9e-7 with the three-dimensional transform), at no cost in time: the
+// twiddle table lies in LDS and frees the registers the preloaded ones held.
+template <typename T, int L, int R, class V, class TW>
+__device__ __forceinline__ void convolve_exact(T* re, T* im, int j, const V& lds, const TW& tw, const T* g,
+                                               const T* gl) {
+  fft_forward<T, L, R>(re, im, j, lds, tw);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const Cx<T> a = src[j + r * (L / 4)];
-          const Cx<T> w = tw[r * step];
-          const T c = w.re, s = dir > 0 ? w.im : -w.im;
-          vr[r] = a.re * c - a.im * s;
-          vi[r] = a.re * s + a.im * c;
-        }
-        // 4-point DFT with i^dir: (dir i) v = (-dir vi, dir vr)
-        const T dr = T(dir);
-        const T s02r = vr[0] + vr[2], s02i = vi[0] + vi[2], d02r = vr[0] - vr[2], d02i = vi[0] - vi[2];
-        const T s13r = vr[1] + vr[3], s13i = vi[1] + vi[3], d13r = vr[1] - vr[3], d13i = vi[1] - vi[3];
-        const int d = (j / Ns) * Ns * 4 + k;
-        dst[d].re = s02r + s13r;
-        dst[d].im = s02i + s13i;
-        dst[d + Ns].re = d02r - dr * d13i;
-        dst[d + Ns].im = d02i + dr * d13r;
-        dst[d + 2 * Ns].re = s02r - s13r;
-        dst[d + 2 * Ns].im = s02i - s13i;
-        dst[d + 3 * Ns].re = d02r + dr * d13i;
-        dst[d + 3 * Ns].im = d02i - dr * d13r;
-      }
-    }
-    __syncthreads();
-    Cx<T>* tmp = src;
-    src = dst;
-    dst = tmp;
-  }
-  *out = src;
-}
-
-// Transform every line of C in place.  Contiguous lines (A.lb == 0): TL =
-// max(L/2, 1) consecutive threads per line, kThreads / TL lines per block.
-// Strided lines (A.lb > 0): A.lb lines per block, interleaved across lanes
-// (lane % lb picks the line), so that the lanes of one load instruction read
-// neighbouring lines' elements: consecutive addresses.  Dynamic LDS
-// lines * (2 L + 2) complex values (the 2 pad the lines across banks), then
-// the L twiddles.
-template <typename T>
-__global__ void __launch_bounds__(kThreads) k_p3_fft(Cx<T>* __restrict__ C, LineArgs A) {
-  extern __shared__ __align__(16) unsigned char lds_raw[];
-  const int L = A.L;
-  const int lines = A.lb > 0 ? A.lb : kThreads / (L > 1 ? L / 2 : 1);
-  const int TL = kThreads / lines;
-  const int sub = A.lb > 0 ? int(threadIdx.x) % lines : int(threadIdx.x) / TL;
-  const int t = A.lb > 0 ? int(threadIdx.x) / lines : int(threadIdx.x) % TL;
-  const long l = long(blockIdx.x) * lines + sub;
-  const bool active = l < A.count;
-  Cx<T>* base_lds = reinterpret_cast<Cx<T>*>(lds_raw);
-  Cx<T>* b0 = base_lds + long(sub) * (2 * L + 2);
-  Cx<T>* b1 = b0 + L;
-  Cx<T>* tw = base_lds + long(lines) * (2 * L + 2);
-  for (int m = threadIdx.x; m < L; m += kThreads) {
-    T sv, cv;
-    sin_cos_pi(L > 1 ? T(2 * m) / T(L) : T(0), &sv, &cv);
-    tw[m].re = cv;
-    tw[m].im = sv;
-  }
-  const long base = active ? (l / A.g) * A.gs + (l % A.g) * A.gi : 0;
-  const T* wA = static_cast<const T*>(A.wA);
-  const T* wB = static_cast<const T*>(A.wB);
-  if (active) {
-    if (A.fuse == 1) {
-      const T* q = static_cast<const T*>(A.q);
-      for (int e = t; e < L; e += TL) {
-        const long i = base + e * A.st;
-        const T f = half_step_factor(wA[i], wB[i], T(A.a), A.sums, A.inv_n);
-        b0[e].re = q ? f * q[i] : f;
-        b0[e].im = T(0);
-      }
+  for (int m = 0; m < R; ++m) {
+    if constexpr (sizeof(T) == 4) {
+      re[m] = fma(re[m], g[m], re[m] * gl[m]);
+      im[m] = fma(im[m], g[m], im[m] * gl[m]);
     } else {
-      for (int e = t; e < L; e += TL) b0[e] = C[base + e * A.st];
+      re[m] *= g[m];
+      im[m] *= g[m];
     }
   }
-  __syncthreads();
-  Cx<T>* res;
-  stockham(b0, b1, tw, L, t, TL, active, A.mode == 1 ? 1 : -1, &res);
-  if (A.mode == 2) {
-    // heat multiplier at (mx, my, mz); this pass runs along z
-    if (active) {
-      const int x = int(base % A.nx), y = int(base / A.nx);
-      const int mx = x < (A.nx + 1) / 2 ? x : x - A.nx, my = y < (A.ny + 1) / 2 ? y : y - A.ny;
-      const double kxy = double(mx) * mx / (double(A.nx) * A.nx) + double(my) * my / (double(A.ny) * A.ny);
-      const T fxy = T(exp(-A.heat * kxy));  // the factor separates: exp(-h kxy) exp(-h kz)
-      const T hz = T(A.heat / (double(L) * L));
-      for (int e = t; e < L; e += TL) {
-        const int mz = e < (L + 1) / 2 ? e : e - L;
-        const T f = fxy * exp(-hz * T(mz * mz));
-        res[e].re *= f;
-        res[e].im *= f;
-      }
-    }
-    __syncthreads();
-    Cx<T>* other = res == b0 ? b1 : b0;
-    stockham(res, other, tw, L, t, TL, active, 1, &res);
-  }
+  fft_inverse<T, L, R>(re, im, j, lds, tw);
+}
+
+// CONTIG: lines along x, two neighbouring rows per transform, nf = blockDim /
+// (L/R) transforms per block.  Otherwise lines along y or z, columns x, x + 1
+// per transform, NF transforms per block interleaved lane by lane.
+template <typename T, int L, int R, bool CONTIG, int NF>
+__global__ void __launch_bounds__(512) k_p3_pass(PassArgs<T> P) {
+  constexpr int TL = L / R;
+  using V = LdsView<T, L, R, CONTIG, NF>;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ double red[16];
+  const int f = CONTIG ? int(threadIdx.x) / TL : int(threadIdx.x) % NF;
+  const int j = CONTIG ? int(threadIdx.x) % TL : int(threadIdx.x) / NF;
+  const int nf = CONTIG ? int(blockDim.x) / TL : NF;
+  V lds{reinterpret_cast<T2<T>*>(smem_raw), f};
+  const int lt = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+  const int c = lt / gridDim.x, tile = lt % gridDim.x;
+  const long u = long(tile) * nf + f;
+  const bool active = u < P.units;
+  // the two real lines: element e at i0 + e st and i1 + e st
+  long i0 = 0, i1 = 0;
+  bool two = active;
   if (active) {
-    if (A.fuse == 2) {
-      T* qn = static_cast<T*>(A.qn);
-      for (int e = t; e < L; e += TL) {
-        const long i = base + e * A.st;
-        qn[i] = half_step_factor(wA[i], wB[i], T(A.a), A.sums, A.inv_n) * res[e].re * T(A.inv_n);
-      }
+    if constexpr (CONTIG) {
+      i0 = 2 * u * L;
+      i1 = i0 + L;
+      two = 2 * u + 1 < P.rows;
     } else {
-      for (int e = t; e < L; e += TL) C[base + e * A.st] = res[e];
+      i0 = (u / P.inner) * P.gs + 2 * (u % P.inner);
     }
   }
-}
-
-// part[block] = sum over the block's grid-stride elements of a (exp_shift:
-// of exp(-(a - sums[0] inv_n)) instead), FP64, fixed-order block reduction.
-template <typename T>
-__global__ void __launch_bounds__(kThreads) k_p3_sum(const T* __restrict__ a, long n, int expo,
-                                                     const double* __restrict__ sums, double inv_n,
-                                                     double* __restrict__ part) {
-  __shared__ double red[kThreads];
-  const double c = expo ? sums[0] * inv_n : 0.0;
-  double acc = 0.0;
-  for (long i = long(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += long(gridDim.x) * blockDim.x)
-    acc += expo ? double(exp(-(a[i] - T(c)))) : double(a[i]);
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = kThreads / 2; s > 0; s /= 2) {
-    if (int(threadIdx.x) < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
+  const long st = CONTIG ? 1 : P.st;
+  const T ca = T(P.sums[0] * P.inv_n), cb = T(P.sums[1] * P.inv_n);
+  const T fr0 = c == 0 ? P.frac[0][0] : P.frac[1][0], fr1 = c == 0 ? P.frac[0][1] : P.frac[1][1];
+  // both lines' values at element e; the strided pair is one aligned load
+  auto load2 = [&](const T* p, int e, T& a, T& b) {
+    if constexpr (CONTIG) {
+      a = active ? p[i0 + e] : T(0);
+      b = two ? p[i1 + e] : T(0);
+    } else {
+      T2<T> v;
+      v.x = v.y = T(0);
+      if (active) v = *reinterpret_cast<const T2<T>*>(p + i0 + e * st);
+      a = v.x;
+      b = v.y;
+    }
+  };
+  auto store2 = [&](T* p, int e, T a, T b) {
+    if constexpr (CONTIG) {
+      if (active) p[i0 + e] = a;
+      if (two) p[i1 + e] = b;
+    } else if (active) {
+      T2<T> v;
+      v.x = a;
+      v.y = b;
+      *reinterpret_cast<T2<T>*>(p + i0 + e * st) = v;
+    }
+  };
+  auto factor2 = [&](T fr, int e, T& a, T& b) {
+    if (fr == T(1)) {
+      load2(P.EA, e, a, b);
+    } else if (fr == T(0)) {
+      load2(P.EB, e, a, b);
+    } else {
+      T ua, ub, va, vb;
+      load2(P.wA, e, ua, ub);
+      load2(P.wB, e, va, vb);
+      a = boltz(ua, va, fr, ca, cb);
+      b = boltz(ub, vb, fr, ca, cb);
+    }
+  };
+  // twiddles into LDS, behind the transforms' buffer
+  T2<T>* twl = reinterpret_cast<T2<T>*>(smem_raw) + (L > R ? V::size_elems(nf) : 0);
+  for (int i = threadIdx.x; i < TwTables<T, L, R>::kElems; i += blockDim.x) twl[i] = P.tw[i];
+  const TwTables<T, L, R> tw{twl};
+  T g[R], gl[R];
+#pragma unroll
+  for (int m = 0; m < R; ++m) {
+    g[m] = P.mult[j + TL * m];
+    gl[m] = sizeof(T) == 4 ? P.mult[L + j + TL * m] : T(0);
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+  T* tmp = P.tmp + c * P.n;
+  T re[R], im[R], ea[R], eb[R];
+  if (P.first) {
+    // the factor planes of the later passes: A's from the forward chain's
+    // blocks, B's from the backward chain's
+    const T pure = c == 0 ? T(1) : T(0);
+    T* Ep = c == 0 ? P.EA : P.EB;
+#pragma unroll
+    for (int m = 0; m < R; ++m) {
+      const int e = j + TL * m;
+      T ua, ub, va, vb;
+      load2(P.wA, e, ua, ub);
+      load2(P.wB, e, va, vb);
+      const T p0 = boltz(ua, va, pure, ca, cb), p1 = boltz(ub, vb, pure, ca, cb);
+      store2(Ep, e, p0, p1);
+      re[m] = fr0 == pure ? p0 : boltz(ua, va, fr0, ca, cb);
+      im[m] = fr0 == pure ? p1 : boltz(ub, vb, fr0, ca, cb);
+      if (!active) re[m] = T(0);
+      if (!two) im[m] = T(0);
+    }
+  } else {
+#pragma unroll
+    for (int m = 0; m < R; ++m) load2(tmp, j + TL * m, re[m], im[m]);
+  }
+  if (P.mid) {  // loaded before the transform, so that the latency overlaps it
+#pragma unroll
+    for (int m = 0; m < R; ++m) factor2(fr0, j + TL * m, ea[m], eb[m]);
+  }
+  if (P.conv) convolve_exact<T, L, R>(re, im, j, lds, tw, g, gl);
+  double qsum = 0.0;
+  if (P.mid) {
+    T* qo = c == 0 ? P.q[0] : P.q[1];
+#pragma unroll
+    for (int m = 0; m < R; ++m) {
+      re[m] *= ea[m];
+      im[m] *= eb[m];
+      store2(qo, j + TL * m, re[m], im[m]);
+      qsum += double(re[m]) + double(im[m]);
+    }
+    if (P.second) {
+      if (fr1 != fr0) {
+#pragma unroll
+        for (int m = 0; m < R; ++m) factor2(fr1, j + TL * m, ea[m], eb[m]);
+      }
+#pragma unroll
+      for (int m = 0; m < R; ++m) {
+        re[m] *= ea[m];
+        im[m] *= eb[m];
+      }
+      if (P.second == 1) convolve_exact<T, L, R>(re, im, j, lds, tw, g, gl);
+    }
+  }
+  if (!P.mid || P.second) {
+#pragma unroll
+    for (int m = 0; m < R; ++m) store2(tmp, j + TL * m, re[m], im[m]);
+  }
+  if (P.last && c == 0) {
+    double v[1] = {qsum};
+    block_partial<1>(v, red, P.partials, tile);
+  }
 }
 
-// out[0] = sum of part[0..nb) in slot order.  One block.
+// A grid of one site: K is the identity, q_{j+1} = E_j^2 q_j.
+template <typename T>
+__global__ void k_p3_one(PassArgs<T> P, T* q, int chain) {
+  if (threadIdx.x || blockIdx.x) return;
+  const T ca = T(P.sums[0] * P.inv_n), cb = T(P.sums[1] * P.inv_n);
+  const T e = boltz(P.wA[0], P.wB[0], P.frac[chain][0], ca, cb);
+  q[0] = e * (e * (P.first ? T(1) : P.tmp[chain]));
+  P.tmp[chain] = q[0];
+  if (P.last && chain == 0) P.partials[0] = double(q[0]);
+}
+
+// Block sums over grid-stride elements, FP64, in fixed slots [block][NV].
+// gauge = nullptr: of the NV planes of a (n apart); else of exp(-(a - c)) with
+// c the mean from gauge[0].  Four elements per thread in flight.
+template <typename T, int NV>
+__global__ void __launch_bounds__(kThreads) k_p3_sums(const T* __restrict__ a, long n, const double* __restrict__ gauge,
+                                                      double inv_n, double* __restrict__ part) {
+  __shared__ double red[16 * NV];
+  const T c = gauge ? T(gauge[0] * inv_n) : T(0);
+  double acc[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) acc[v] = 0.0;
+  const long step = long(gridDim.x) * blockDim.x;
+  for (long i0 = long(blockIdx.x) * blockDim.x + threadIdx.x; i0 < n; i0 += 4 * step) {
+    T x[4][NV];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int v = 0; v < NV; ++v) x[k][v] = i0 + k * step < n ? a[v * n + i0 + k * step] : T(0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (i0 + k * step < n)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) acc[v] += double(gauge ? exp(-(x[k][v] - c)) : x[k][v]);
+  }
+  block_partial<NV>(acc, red, part, blockIdx.x);
+}
+
+// out[v] = sum over blocks of part[block][v] in slot order.  One block.
+template <int NV>
 __global__ void __launch_bounds__(kThreads) k_p3_finish(const double* __restrict__ part, int nb,
                                                         double* __restrict__ out) {
-  __shared__ double red[kThreads];
-  double acc = 0.0;
-  for (int b = threadIdx.x; b < nb; b += blockDim.x) acc += part[b];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = kThreads / 2; s > 0; s /= 2) {
-    if (int(threadIdx.x) < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[0] = red[0];
-}
-
-template <typename T>
-__global__ void __launch_bounds__(kThreads) k_p3_fill(T* __restrict__ a, T v, long n) {
-  for (long i = long(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += long(gridDim.x) * blockDim.x) a[i] = v;
+  __shared__ double red[16 * NV];
+  double acc[NV];
+  sum_partials<NV>(part, nb, acc, red);
+  if (threadIdx.x == 0)
+#pragma unroll
+    for (int v = 0; v < NV; ++v) out[v] = acc[v];
 }
 
 struct DensArgs {
@@ -255,26 +291,31 @@ struct DensArgs {
   double phiP;
   const double* wAn;  // node weights, N + 1 each
   const double* wBn;
-  const double* sums; // [0] sum wA, [2] sum wB, [4] sum wS, [6] sum q_N, [8] sum exp(-(wS - cS))
+  const double* sums; // [0] sum wA, [1] sum wB, [2] sum wS, [3] sum q_N, [4] sum exp(-(wS - cS))
   double inv_n;
 };
 
 // Phi_A = (V phibar_P / Q_P) sum_j wA_j q_j qb_{N-j}, Phi_B likewise, Phi_S =
 // V (1 - phibar_P) exp(-(wS - cS)) / Q_S, with Q = dV * sum (dV cancels).
+// q and qb hold the planes q_1 .. q_N (q_0 = 1).
 template <typename T>
 __global__ void __launch_bounds__(kThreads) k_p3_density(const T* __restrict__ q, const T* __restrict__ qb,
                                                          const T* __restrict__ wS, T* __restrict__ phi,
                                                          DensArgs D) {
-  const double sP = D.V_over_dV * D.phiP / D.sums[6];
-  const double sS = D.V_over_dV * (1.0 - D.phiP) / D.sums[8];
-  const T cS = T(D.sums[4] * D.inv_n);
+  const double sP = D.V_over_dV * D.phiP / D.sums[3];
+  const double sS = D.V_over_dV * (1.0 - D.phiP) / D.sums[4];
+  const T cS = T(D.sums[2] * D.inv_n);
   for (long i = long(blockIdx.x) * blockDim.x + threadIdx.x; i < D.n; i += long(gridDim.x) * blockDim.x) {
-    T sa = T(0), sb = T(0);
-    for (int j = 0; j <= D.N; ++j) {
-      const T pr = q[long(j) * D.n + i] * qb[long(D.N - j) * D.n + i];
+    const T q0 = qb[long(D.N - 1) * D.n + i], qN = q[long(D.N - 1) * D.n + i];
+    T sa = T(D.wAn[0]) * q0, sb = T(D.wBn[0]) * q0;
+#pragma unroll 8
+    for (int j = 1; j < D.N; ++j) {
+      const T pr = q[long(j - 1) * D.n + i] * qb[long(D.N - j - 1) * D.n + i];
       sa += T(D.wAn[j]) * pr;
       sb += T(D.wBn[j]) * pr;
     }
+    sa += T(D.wAn[D.N]) * qN;
+    sb += T(D.wBn[D.N]) * qN;
     phi[i] = T(sP) * sa;
     phi[D.n + i] = T(sP) * sb;
     phi[2 * D.n + i] = T(sS) * exp(-(wS[i] - cS));

@@ -3371,14 +3371,20 @@ struct epdlb_epd3 {
   int N = 0;
   double f_A = 0.5, phi_P = 0.1, R_G = 1.0, dx = 1.0;
   int precision = 0;
+  // The sides above 1, fastest first (an axis of one site has no wavenumber
+  // but 0, so dropping it changes neither the layout nor the kernel).
+  int ndim = 0;
+  int len[3] = {1, 1, 1};
   void* mem = nullptr;
   void* w = nullptr;    // 3 planes
   void* phi = nullptr;  // 3 planes
-  void* q = nullptr;    // N + 1 planes
-  void* qb = nullptr;   // N + 1 planes
-  void* C = nullptr;    // n complex
+  void* q = nullptr;    // planes q_1 .. q_N
+  void* qb = nullptr;   // planes q'_1 .. q'_N
+  void* tmp = nullptr;  // 2 planes, one per chain
+  void* E = nullptr;    // 2 planes: half-step factors of A and B segments
+  void* tab[3] = {nullptr, nullptr, nullptr};  // per axis (see p3_tables)
   double* part = nullptr;
-  double* sums = nullptr;  // 16
+  double* sums = nullptr;  // 8
   double* nodes = nullptr; // wA_j, wB_j: 2 (N + 1)
   std::vector<double> seg;  // A-content of each contour segment
   std::vector<hipEvent_t> ev;  // start/stop pairs of the timed FFT launches (epdlb_epd3_profile)
@@ -3393,103 +3399,176 @@ namespace {
 
 bool pow2_upto(int v, int m) { return v >= 1 && v <= m && (v & (v - 1)) == 0; }
 
-template <typename T>
-int p3_fft(epdlb_epd3* c, int axis, int mode, int fuse = 0, const T* q = nullptr, T* qn = nullptr, T a = T(0)) {
-  epd3::LineArgs A;
-  const long n = c->n;
-  A.fuse = fuse;
-  A.wA = c->w;
-  A.wB = static_cast<const T*>(c->w) + n;
-  A.q = q;
-  A.qn = qn;
-  A.sums = c->sums;
-  A.inv_n = 1.0 / double(n);
-  A.a = double(a);
-  A.nx = c->nx;
-  A.ny = c->ny;
-  A.nz = c->nz;
-  A.mode = mode;
-  A.heat = c->R_G * c->R_G / c->N * (2.0 * M_PI / c->dx) * (2.0 * M_PI / c->dx);
-  if (axis == 0) {
-    A.L = c->nx; A.st = 1; A.count = long(c->ny) * c->nz; A.g = 1; A.gs = c->nx; A.gi = 0;
-  } else if (axis == 1) {
-    A.L = c->ny; A.st = c->nx; A.count = long(c->nx) * c->nz; A.g = c->nx; A.gs = long(c->nx) * c->ny; A.gi = 1;
-  } else {
-    A.L = c->nz; A.st = long(c->nx) * c->ny; A.count = long(c->nx) * c->ny; A.g = 1; A.gs = 1; A.gi = 0;
-  }
-  if (A.L == 1 && mode != 2 && fuse == 0) return EPDLB_OK;  // a transform of length 1 is the identity
-  // strided lines (y, z): up to 16 neighbouring lines per block, interleaved
-  // across lanes, with the LDS held to 96 KB; contiguous lines (x): half a
-  // line's length of threads per line
-  A.lb = 0;
-  if (axis > 0) {
-    long lb = 16;
-    while (lb > 1 && (size_t(lb) * (2 * A.L + 2) + A.L) * sizeof(epd3::Cx<T>) > 98304) lb /= 2;
-    A.lb = int(lb);
-  }
-  const long lines = A.lb > 0 ? A.lb : epd3::kThreads / (A.L > 1 ? A.L / 2 : 1);
-  const size_t lds = (size_t(lines) * (2 * A.L + 2) + A.L) * sizeof(epd3::Cx<T>);
-  const long blocks = (A.count + lines - 1) / lines;
-  HIPCHK(prep_lds(epd3::k_p3_fft<T>, lds));
-  if (c->profiling && 2 * c->ev_used + 1 < c->ev.size()) {
-    tl_ev_start = c->ev[2 * c->ev_used];
-    tl_ev_stop = c->ev[2 * c->ev_used + 1];
-    ++c->ev_used;
-  }
-  launch_k((epd3::k_p3_fft<T>), dim3(unsigned(blocks)), dim3(epd3::kThreads), lds, c->stream,
-           static_cast<epd3::Cx<T>*>(c->C), A);
+// Blocks per chain of a pass along `axis` over lines of length L.
+template <typename T, int L, bool CONTIG> struct P3Shape {
+  static constexpr int R = epd3::values_per_lane<L>();
+  static constexpr int nf = CONTIG ? 256 / (L / R) : epd3::strided_nf<T, L, R>();
+  static constexpr int threads = nf * (L / R);
+  // the transforms' exchange buffer, then the twiddles; none for one-pass transforms
+  static constexpr size_t lds =
+      L > R ? (LdsView<T, L, R, CONTIG, CONTIG ? 1 : nf>::size_elems(nf) + TwTables<T, L, R>::kElems) * sizeof(T2<T>)
+            : 0;
+};
+
+template <typename T, int L, bool CONTIG>
+int p3_pass_shape(const epd3::PassArgs<T>* a, hipStream_t s, long units, long* blocks) {
+  using S = P3Shape<T, L, CONTIG>;
+  *blocks = (units + S::nf - 1) / S::nf;
+  if (!a) return EPDLB_OK;
+  auto k = epd3::k_p3_pass<T, L, S::R, CONTIG, CONTIG ? 1 : S::nf>;
+  HIPCHK(prep_lds(k, S::lds));
+  launch_k(k, dim3(unsigned(*blocks), 2), dim3(S::threads), S::lds, s, *a);
   HIPCHK(hipGetLastError());
   return EPDLB_OK;
 }
 
-template <typename T> int p3_sum(epdlb_epd3* c, const T* a, int expo, const double* shift_sum, double* out) {
-  launch_k((epd3::k_p3_sum<T>), dim3(epd3::kRedBlocks), dim3(epd3::kThreads), 0, c->stream, a, c->n, expo,
-           shift_sum, 1.0 / double(c->n), c->part);
+// One pass along axis `ax` of the grid (a = nullptr: only its blocks per chain).
+template <typename T> int p3_pass(epdlb_epd3* c, int ax, epd3::PassArgs<T>* a, long* blocks) {
+  const int L = c->len[ax];
+  const long lines = c->n / L;
+  const long units = (lines + 1) / 2;
+  if (a) {
+    const T* t = static_cast<const T*>(c->tab[ax]);
+    a->mult = t;
+    a->tw = reinterpret_cast<const T2<T>*>(t + 2 * L);
+    a->units = units;
+    a->rows = lines;
+    a->st = ax == 0 ? 1 : (ax == 1 ? c->len[0] : long(c->len[0]) * c->len[1]);
+    a->inner = a->st / 2;  // the fastest side is even
+    if (a->inner < 1) a->inner = 1;
+    a->gs = a->st * L;
+    if (c->profiling && 2 * c->ev_used + 1 < c->ev.size()) {
+      tl_ev_start = c->ev[2 * c->ev_used];
+      tl_ev_stop = c->ev[2 * c->ev_used + 1];
+      ++c->ev_used;
+    }
+  }
+#define EPDLB_P3_L(len)                                                                     \
+  case len:                                                                                 \
+    return ax == 0 ? p3_pass_shape<T, len, true>(a, c->stream, units, blocks)               \
+                   : p3_pass_shape<T, len, false>(a, c->stream, units, blocks);
+  switch (L) {
+    EPDLB_P3_L(2)
+    EPDLB_P3_L(4)
+    EPDLB_P3_L(8)
+    EPDLB_P3_L(16)
+    EPDLB_P3_L(32)
+    EPDLB_P3_L(64)
+    EPDLB_P3_L(128)
+    EPDLB_P3_L(256)
+    EPDLB_P3_L(512)
+  }
+#undef EPDLB_P3_L
+  return fail(EPDLB_EINVAL, "unsupported line length");
+}
+
+// The axis of convolution k of contour step a: x, y, z on even steps, z, y, x on odd ones.
+int p3_axis(const epdlb_epd3* c, int a, int k) { return a % 2 == 0 ? k : c->ndim - 1 - k; }
+
+template <typename T, int NV>
+int p3_sum(epdlb_epd3* c, const T* a, const double* gauge, double* out) {
+  const int blocks = int(std::min<long>(epd3::kRedBlocks, (c->n + epd3::kThreads - 1) / epd3::kThreads));
+  launch_k((epd3::k_p3_sums<T, NV>), dim3(blocks), dim3(epd3::kThreads), 0, c->stream, a, c->n, gauge,
+           1.0 / double(c->n), c->part);
   HIPCHK(hipGetLastError());
-  launch_k(epd3::k_p3_finish, dim3(1), dim3(epd3::kThreads), 0, c->stream, static_cast<const double*>(c->part),
-           epd3::kRedBlocks, out);
+  launch_k(epd3::k_p3_finish<NV>, dim3(1), dim3(epd3::kThreads), 0, c->stream, static_cast<const double*>(c->part),
+           blocks, out);
   HIPCHK(hipGetLastError());
   return EPDLB_OK;
 }
 
 template <typename T> int p3_densities(epdlb_epd3* c) {
   const long n = c->n;
+  const int N = c->N;
   const T* w = static_cast<const T*>(c->w);
-  const T *wA = w, *wB = w + n, *wS = w + 2 * n;
-  const double inv_n = 1.0 / double(n);
-  const dim3 eg(unsigned(std::min<long>((n + epd3::kThreads - 1) / epd3::kThreads, 4096)));
-  CHK(p3_sum<T>(c, wA, 0, nullptr, c->sums + 0));
-  CHK(p3_sum<T>(c, wB, 0, nullptr, c->sums + 2));
-  CHK(p3_sum<T>(c, wS, 0, nullptr, c->sums + 4));
-  for (int chain = 0; chain < 2; ++chain) {
-    T* q = static_cast<T*>(chain ? c->qb : c->q);
-    launch_k((epd3::k_p3_fill<T>), eg, dim3(epd3::kThreads), 0, c->stream, q, T(1), n);
-    HIPCHK(hipGetLastError());
-    for (int j = 0; j < c->N; ++j) {
-      const int seg = chain ? c->N - 1 - j : j;
-      const T a = T(c->seg[seg]);
-      // the half-step factors ride on the x passes: E q as the lines load, E Re / n as they store
-      CHK(p3_fft<T>(c, 0, -1, 1, static_cast<const T*>(q + long(j) * n), nullptr, a));
-      CHK(p3_fft<T>(c, 1, -1));
-      CHK(p3_fft<T>(c, 2, 2));
-      CHK(p3_fft<T>(c, 1, 1));
-      CHK(p3_fft<T>(c, 0, 1, 2, nullptr, q + long(j + 1) * n, a));
+  T* q[2] = {static_cast<T*>(c->q), static_cast<T*>(c->qb)};
+  CHK((p3_sum<T, 3>(c, w, nullptr, c->sums)));
+  CHK((p3_sum<T, 1>(c, w + 2 * n, c->sums + 2, c->sums + 4)));
+  epd3::PassArgs<T> A{};
+  A.wA = w;
+  A.wB = w + n;
+  A.EA = static_cast<T*>(c->E);
+  A.EB = A.EA + n;
+  A.sums = c->sums;
+  A.inv_n = 1.0 / double(n);
+  A.tmp = static_cast<T*>(c->tmp);
+  A.n = n;
+  A.partials = c->part;
+  auto seg = [&](int chain, int step) { return T(c->seg[chain ? N - 1 - step : step]); };
+  long blocks = 1;
+  if (c->ndim == 0) {
+    for (int s = 0; s < N; ++s)
+      for (int ch = 0; ch < 2; ++ch) {
+        A.first = s == 0;
+        A.last = s + 1 == N;
+        A.frac[ch][0] = seg(ch, s);
+        launch_k((epd3::k_p3_one<T>), dim3(1), dim3(64), 0, c->stream, A, q[ch] + s, ch);
+        HIPCHK(hipGetLastError());
+      }
+  } else {
+    // step 0: its first convolution, of E(step 0); with one axis only E itself
+    A.first = 1;
+    A.conv = c->ndim > 1;
+    for (int ch = 0; ch < 2; ++ch) A.frac[ch][0] = A.frac[ch][1] = seg(ch, 0);
+    CHK(p3_pass<T>(c, 0, &A, &blocks));
+    A.first = 0;
+    A.conv = 1;
+    for (int s = 0; s < N; ++s) {
+      // the convolutions of step s between its first and its last
+      A.mid = A.second = A.last = 0;
+      for (int k = 1; k + 1 < c->ndim; ++k) CHK(p3_pass<T>(c, p3_axis(c, s, k), &A, &blocks));
+      // its last one, shared with the first one of step s + 1
+      A.mid = 1;
+      A.second = s + 1 == N ? 0 : (c->ndim > 1 ? 1 : 2);
+      A.last = s + 1 == N;
+      for (int ch = 0; ch < 2; ++ch) {
+        A.q[ch] = q[ch] + long(s) * n;
+        A.frac[ch][0] = seg(ch, s);
+        A.frac[ch][1] = s + 1 < N ? seg(ch, s + 1) : seg(ch, s);
+      }
+      CHK(p3_pass<T>(c, p3_axis(c, s, c->ndim - 1), &A, &blocks));
     }
   }
-  CHK(p3_sum<T>(c, static_cast<const T*>(c->q) + long(c->N) * n, 0, nullptr, c->sums + 6));
-  CHK(p3_sum<T>(c, wS, 1, c->sums + 4, c->sums + 8));
+  launch_k(epd3::k_p3_finish<1>, dim3(1), dim3(epd3::kThreads), 0, c->stream, static_cast<const double*>(c->part),
+           int(blocks), c->sums + 3);
+  HIPCHK(hipGetLastError());
   epd3::DensArgs D;
-  D.N = c->N;
+  D.N = N;
   D.n = n;
   D.V_over_dV = double(n);
   D.phiP = c->phi_P;
   D.wAn = c->nodes;
-  D.wBn = c->nodes + (c->N + 1);
+  D.wBn = c->nodes + (N + 1);
   D.sums = c->sums;
-  D.inv_n = inv_n;
-  launch_k((epd3::k_p3_density<T>), eg, dim3(epd3::kThreads), 0, c->stream, static_cast<const T*>(c->q),
-           static_cast<const T*>(c->qb), wS, static_cast<T*>(c->phi), D);
+  D.inv_n = A.inv_n;
+  const dim3 eg(unsigned(std::min<long>((n + epd3::kThreads - 1) / epd3::kThreads, 4096)));
+  launch_k((epd3::k_p3_density<T>), eg, dim3(epd3::kThreads), 0, c->stream, static_cast<const T*>(q[0]),
+           static_cast<const T*>(q[1]), w + 2 * n, static_cast<T*>(c->phi), D);
   HIPCHK(hipGetLastError());
+  return EPDLB_OK;
+}
+
+// Tables of axis ax: multipliers exp(-R_G^2 k^2 ds)/L, what their rounding to
+// T left, then the twiddles.
+template <typename T> int p3_tables(epdlb_epd3* c, int ax) {
+  const int L = c->len[ax];
+  std::vector<T> t(2 * size_t(L));
+  for (int e = 0; e < L; ++e) {
+    const double k = 2.0 * M_PI * (e < L / 2 ? e : e - L) / (L * c->dx);
+    const double g = std::exp(-c->R_G * c->R_G * k * k / c->N) / L;
+    t[size_t(e)] = T(g);
+    t[size_t(L) + size_t(e)] = T(g - double(T(g)));
+  }
+  switch (L) {
+    case 16: TwTables<T, 16, 8>::fill(t); break;
+    case 32: TwTables<T, 32, 8>::fill(t); break;
+    case 64: TwTables<T, 64, 8>::fill(t); break;
+    case 128: TwTables<T, 128, 8>::fill(t); break;
+    case 256: TwTables<T, 256, 8>::fill(t); break;
+    case 512: TwTables<T, 512, 8>::fill(t); break;
+  }
+  HIPCHK(hipMemcpyAsync(c->tab[ax], t.data(), t.size() * sizeof(T), hipMemcpyHostToDevice, c->stream));
+  HIPCHK(hipStreamSynchronize(c->stream));
   return EPDLB_OK;
 }
 
@@ -3544,11 +3623,22 @@ int epdlb_epd3_create(int32_t nx, int32_t ny, int32_t nz, int32_t n_contour, dou
       nodes[N + 1 + j] += 0.5 * ds * (1.0 - c->seg[j]);
     }
   }
+  for (int side : {nx, ny, nz})
+    if (side > 1) c->len[c->ndim++] = side;
+  // partial sums: the field sums' slots, or one per block of the last pass
+  long blocks = 1;
+  if (c->ndim > 0) {
+    const int last = p3_axis(c, N - 1, c->ndim - 1);
+    if (precision)
+      (void)p3_pass<float>(c, last, nullptr, &blocks);
+    else
+      (void)p3_pass<double>(c, last, nullptr, &blocks);
+  }
+  const size_t part_bytes = align256(std::max<size_t>(3 * epd3::kRedBlocks, size_t(blocks)) * sizeof(double));
   const size_t plane = align256(size_t(c->n) * c->es());
-  const size_t cbytes = align256(size_t(c->n) * 2 * c->es());
-  const size_t total = 3 * plane + 3 * plane + 2 * size_t(N + 1) * plane + cbytes +
-                       align256(epd3::kRedBlocks * sizeof(double)) + align256(16 * sizeof(double)) +
-                       align256(nodes.size() * sizeof(double));
+  const size_t tab_bytes = align256(6 * size_t(epd3::kMaxLen) * c->es());
+  const size_t total = (3 + 3 + 2 * size_t(N) + 2 + 2) * plane + 3 * tab_bytes + part_bytes +
+                       align256(8 * sizeof(double)) + align256(nodes.size() * sizeof(double));
   if (hipMalloc(&c->mem, total) != hipSuccess) {
     delete c;
     return fail(EPDLB_ENOMEM, "hipMalloc of the propagator planes failed");
@@ -3559,15 +3649,21 @@ int epdlb_epd3_create(int32_t nx, int32_t ny, int32_t nz, int32_t n_contour, dou
   c->phi = b;
   b += 3 * plane;
   c->q = b;
-  b += size_t(N + 1) * plane;
+  b += size_t(N) * plane;
   c->qb = b;
-  b += size_t(N + 1) * plane;
-  c->C = b;
-  b += cbytes;
+  b += size_t(N) * plane;
+  c->tmp = b;
+  b += 2 * plane;
+  c->E = b;
+  b += 2 * plane;
+  for (int ax = 0; ax < 3; ++ax) {
+    c->tab[ax] = b;
+    b += tab_bytes;
+  }
   c->part = reinterpret_cast<double*>(b);
-  b += align256(epd3::kRedBlocks * sizeof(double));
+  b += part_bytes;
   c->sums = reinterpret_cast<double*>(b);
-  b += align256(16 * sizeof(double));
+  b += align256(8 * sizeof(double));
   c->nodes = reinterpret_cast<double*>(b);
   if (stream) {
     c->stream = reinterpret_cast<hipStream_t>(stream);
@@ -3583,6 +3679,13 @@ int epdlb_epd3_create(int32_t nx, int32_t ny, int32_t nz, int32_t n_contour, dou
       hipStreamSynchronize(c->stream) != hipSuccess) {
     epdlb_epd3_destroy(c);
     return fail(EPDLB_EHIP, "uploading the contour weights failed");
+  }
+  for (int ax = 0; ax < c->ndim; ++ax) {
+    const int r = precision ? p3_tables<float>(c, ax) : p3_tables<double>(c, ax);
+    if (r != EPDLB_OK) {
+      epdlb_epd3_destroy(c);
+      return r;
+    }
   }
   *out = c;
   return EPDLB_OK;
@@ -3608,13 +3711,13 @@ int epdlb_epd3_densities(epdlb_epd3* c, const double* omega, double* phi, double
     HIPCHK(hipMemcpyAsync(phi, c->phi, 3 * n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
   }
-  double s[16];
+  double s[8];
   HIPCHK(hipMemcpyAsync(s, c->sums, sizeof(s), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   const double dV = c->dx * c->dx * c->dx;
-  if (Q_P) *Q_P = dV * s[6];
-  if (Q_S) *Q_S = dV * s[8];
-  if (!std::isfinite(s[6]) || !std::isfinite(s[8]) || !(s[6] > 0.0))
+  if (Q_P) *Q_P = dV * s[3];
+  if (Q_S) *Q_S = dV * s[4];
+  if (!std::isfinite(s[3]) || !std::isfinite(s[4]) || !(s[3] > 0.0))
     return fail(EPDLB_ENONFINITE, "a partition function is not finite and positive");
   return EPDLB_OK;
 }
@@ -3645,7 +3748,7 @@ int epdlb_epd3_time(epdlb_epd3* c, int32_t reps, double* ms) {
 int epdlb_epd3_profile(epdlb_epd3* c, double* fft_ms, int32_t* fft_launches) {
   if (!c || !fft_ms || !fft_launches) return fail(EPDLB_EINVAL, "NULL argument");
   HIPCHK(hipSetDevice(c->device));
-  const size_t need = 2 * size_t(10 * c->N + 2);
+  const size_t need = 2 * size_t(2 * c->N + 2);
   while (c->ev.size() < need) {
     hipEvent_t e;
     HIPCHK(hipEventCreate(&e));

@@ -15,6 +15,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cmath>
+#include <vector>
+
 namespace epdlb {
 
 template <typename T> struct vec2;
@@ -179,10 +182,10 @@ struct LdsView {
 // One Stockham pass of radix r over sub-transforms of length Ns.
 // Input element of butterfly jj, leg q: in[jj + q*L/r].  Output element:
 // out[(jj/Ns)*Ns*r + jj%Ns + q*Ns].  FROM_REG / TO_REG: the pass reads /
-// leaves its data in the lane's registers (natural layout j + T*m).
-template <typename T, int L, int R, int r, int Ns, int SIGN, bool FROM_REG, bool TO_REG, class V>
-__device__ __forceinline__ void stockham_pass(T* re, T* im, int j, const V& lds, const T2<T>* w1s,
-                                              const T2<T>* whs) {
+// leaves its data in the lane's registers (natural layout j + T*m).  P: the
+// pass's place in its direction; tw: its twiddles (Twiddles or TwTables).
+template <typename T, int L, int R, int r, int Ns, int SIGN, bool FROM_REG, bool TO_REG, int P, class V, class TW>
+__device__ __forceinline__ void stockham_pass(T* re, T* im, int j, const V& lds, const TW& tw) {
   constexpr int TL = L / R;
   constexpr int SUB = R / r;
   T vr[R], vi[R];
@@ -200,12 +203,21 @@ __device__ __forceinline__ void stockham_pass(T* re, T* im, int j, const V& lds,
         vi[s * r + q] = v.y;
       }
     }
-    if constexpr (Ns > 1) {
+    if constexpr (Ns > 1 && TW::kTable) {
+#pragma unroll
+      for (int q = 1; q < r; ++q) {
+        const T2<T> w = tw.template at<P, SIGN < 0>(q, jj & (Ns - 1));
+        const T ci = SIGN > 0 ? -w.y : w.y;
+        const T x = vr[s * r + q] * w.x - vi[s * r + q] * ci;
+        vi[s * r + q] = vr[s * r + q] * ci + vi[s * r + q] * w.x;
+        vr[s * r + q] = x;
+      }
+    } else if constexpr (Ns > 1) {
       // twiddles W^(k q), k = jj mod Ns, for q = 1..r-1: W^k and W^(k r/2)
       // come preloaded (q >= r/2 restarts from the latter to bound the
       // recurrence); complex products in between
-      const T2<T> w1 = w1s[s];
-      const T2<T> wh = whs[s];
+      const T2<T> w1 = tw.w1[P][s];
+      const T2<T> wh = tw.wh[P][s];
       const T w1y = SIGN > 0 ? -w1.y : w1.y;
       const T why = SIGN > 0 ? -wh.y : wh.y;
       T cr = T(1), ci = T(0);
@@ -267,8 +279,49 @@ template <int L, int R, bool FWD> struct PassInfo<L, R, -1, FWD> {
 // table load: w1[P][s] = W_L^(k e), wh[P][s] = W_L^(k (r/2) e), with
 // k = (j + T s) mod Ns and e = L/(Ns r).
 template <typename T, int L, int R> struct Twiddles {
+  static constexpr bool kTable = false;
   static constexpr int S = Plan<L, R>::S;
   T2<T> w1[S][R], wh[S][R];
+};
+
+// Every twiddle of both directions as a table entry of its own (correctly
+// rounded, where products of preloaded ones carry up to three roundings),
+// ordered by use: pass by pass, leg q = 1..r-1, then k = jj mod Ns, so that
+// the lanes of one access read consecutive (or equal) entries.  The forward
+// passes come first.  Meant for LDS: about 2 L entries, no registers held.
+template <int L, int R, int P, bool FWD> constexpr int tw_table_off() {
+  if constexpr (P == 0) {
+    return 0;
+  } else {
+    using PI = PassInfo<L, R, P - 1, FWD>;
+    return tw_table_off<L, R, P - 1, FWD>() + (PI::Ns > 1 ? (PI::r - 1) * PI::Ns : 0);
+  }
+}
+template <typename T, int L, int R> struct TwTables {
+  static constexpr bool kTable = true;
+  static constexpr int S = Plan<L, R>::S;
+  static constexpr int kFwd = tw_table_off<L, R, S, true>();
+  static constexpr int kElems = kFwd + tw_table_off<L, R, S, false>();
+  const T2<T>* t;
+  template <int P, bool FWD> __device__ __forceinline__ T2<T> at(int q, int k) const {
+    return t[(FWD ? 0 : kFwd) + tw_table_off<L, R, P, FWD>() + (q - 1) * PassInfo<L, R, P, FWD>::Ns + k];
+  }
+  // host: appends (cos, -sin) of the table's angles to out
+  template <bool FWD, int P> static void fill_pass(std::vector<T>& out) {
+    using PI = PassInfo<L, R, P, FWD>;
+    if constexpr (PI::Ns > 1)
+      for (int q = 1; q < PI::r; ++q)
+        for (int k = 0; k < PI::Ns; ++k) {
+          const double ang = kTwoPi * double(k) * q / double(PI::Ns * PI::r);
+          out.push_back(T(std::cos(ang)));
+          out.push_back(T(-std::sin(ang)));
+        }
+    if constexpr (P + 1 < S) fill_pass<FWD, P + 1>(out);
+  }
+  static void fill(std::vector<T>& out) {
+    fill_pass<true, 0>(out);
+    fill_pass<false, 0>(out);
+  }
 };
 template <typename T, int L, int R, int P, bool FWD>
 __device__ __forceinline__ void load_twiddles(Twiddles<T, L, R>& t, int j, const T2<T>* __restrict__ tw) {
@@ -285,11 +338,11 @@ __device__ __forceinline__ void load_twiddles(Twiddles<T, L, R>& t, int j, const
   if constexpr (P + 1 < Plan<L, R>::S) load_twiddles<T, L, R, P + 1, FWD>(t, j, tw);
 }
 
-template <typename T, int L, int R, int P, bool FWD, class V>
-__device__ __forceinline__ void run_passes(T* re, T* im, int j, const V& lds, const Twiddles<T, L, R>& t) {
+template <typename T, int L, int R, int P, bool FWD, class V, class TW>
+__device__ __forceinline__ void run_passes(T* re, T* im, int j, const V& lds, const TW& t) {
   using PI = PassInfo<L, R, P, FWD>;
   constexpr int S = Plan<L, R>::S;
-  stockham_pass<T, L, R, PI::r, PI::Ns, FWD ? -1 : +1, P == 0, P == S - 1>(re, im, j, lds, t.w1[P], t.wh[P]);
+  stockham_pass<T, L, R, PI::r, PI::Ns, FWD ? -1 : +1, P == 0, P == S - 1, P>(re, im, j, lds, t);
   if constexpr (P + 1 < S) run_passes<T, L, R, P + 1, FWD>(re, im, j, lds, t);
 }
 
@@ -306,13 +359,13 @@ __device__ __forceinline__ void load_inv_twiddles(Twiddles<T, L, R>& t, int j, c
 
 // x (time, lane layout j + T*m) -> X (frequency, same layout), radices
 // [R0, R, ..., R].  Every lane of the block must call it.
-template <typename T, int L, int R, class V>
-__device__ __forceinline__ void fft_forward(T* re, T* im, int j, const V& lds, const Twiddles<T, L, R>& t) {
+template <typename T, int L, int R, class V, class TW>
+__device__ __forceinline__ void fft_forward(T* re, T* im, int j, const V& lds, const TW& t) {
   run_passes<T, L, R, 0, true>(re, im, j, lds, t);
 }
 // Inverse (unnormalised), radices [R, ..., R, R0].
-template <typename T, int L, int R, class V>
-__device__ __forceinline__ void fft_inverse(T* re, T* im, int j, const V& lds, const Twiddles<T, L, R>& t) {
+template <typename T, int L, int R, class V, class TW>
+__device__ __forceinline__ void fft_inverse(T* re, T* im, int j, const V& lds, const TW& t) {
   run_passes<T, L, R, 0, false>(re, im, j, lds, t);
 }
 

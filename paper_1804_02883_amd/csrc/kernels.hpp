@@ -203,13 +203,13 @@ __device__ __forceinline__ T2<T> efactor2(const PropArgs<T>& P, T fr, T ca, T cb
 template <typename T, int L, int R, class V>
 __device__ __forceinline__ void convolve(T* re, T* im, int j, const V& lds, const Twiddles<T, L, R>& twf,
                                          const Twiddles<T, L, R>& twi, const T* g) {
-  fft_forward(re, im, j, lds, twf);
+  fft_forward<T, L, R>(re, im, j, lds, twf);
 #pragma unroll
   for (int m = 0; m < R; ++m) {
     re[m] *= g[m];
     im[m] *= g[m];
   }
-  fft_inverse(re, im, j, lds, twi);
+  fft_inverse<T, L, R>(re, im, j, lds, twi);
 }
 
 // x-oriented kernel: rows 2rp and 2rp+1 of one chain packed as one complex
@@ -757,7 +757,7 @@ __global__ void __launch_bounds__(512) k_force_row_fwd(ForceArgs<T> P) {
     re[m] = active ? P.S[long(y) * P.nx + j + TL * m] : T(0);
     im[m] = T(0);
   }
-  fft_forward(re, im, j, lds, twf);
+  fft_forward<T, L, R>(re, im, j, lds, twf);
   if (active) {
 #pragma unroll
     for (int m = 0; m < R; ++m) {
@@ -792,7 +792,7 @@ __global__ void __launch_bounds__(512) k_force_col(ForceArgs<T> P) {
     re[m] = v.x;
     im[m] = v.y;
   }
-  fft_forward(re, im, j, lds, twf);
+  fft_forward<T, L, R>(re, im, j, lds, twf);
   const int mx = kxi < P.nx / 2 ? kxi : kxi - P.nx;
   const double kx = P.kx0 * mx;
   const bool nyq_x = (kxi == P.nx / 2);
@@ -810,7 +810,7 @@ __global__ void __launch_bounds__(512) k_force_col(ForceArgs<T> P) {
     re[m] = -al * si - be * sr;
     im[m] = al * sr - be * si;
   }
-  fft_inverse(re, im, j, lds, twi);
+  fft_inverse<T, L, R>(re, im, j, lds, twi);
   if (active) {
 #pragma unroll
     for (int m = 0; m < R; ++m) {
@@ -844,7 +844,7 @@ __global__ void __launch_bounds__(512) k_force_row_inv(ForceArgs<T> P) {
     re[m] = v.x;
     im[m] = v.y;
   }
-  fft_inverse(re, im, j, lds, twi);
+  fft_inverse<T, L, R>(re, im, j, lds, twi);
   if (active) {
     const T conv = T(P.conv);
     const double g = P.scal[kGext];
@@ -1062,7 +1062,7 @@ __global__ void __launch_bounds__(512) k_force_inv_lb(ForceArgs<T> P, LbArgs<T> 
 #pragma unroll
     for (int m = 0; m < R; ++m) lb_pull(B, j + TL * m, y, g[m]);
   }
-  fft_inverse(re, im, j, lds, twi);
+  fft_inverse<T, L, R>(re, im, j, lds, twi);
   if (!active) return;
   const T conv = T(P.conv);
   const double ge = P.scal[kGext];

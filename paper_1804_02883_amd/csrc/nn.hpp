@@ -1161,7 +1161,7 @@ __global__ void __launch_bounds__(512) k_norm_force_row(ForceArgs<T> F, NormArgs
       atomic_max_nonneg(P.scal + kResidEx, mx[2]);
     }
   }
-  fft_forward(re, im, j, lds, twf);
+  fft_forward<T, L, R>(re, im, j, lds, twf);
   if (in) {
 #pragma unroll
     for (int m = 0; m < R; ++m) {

@@ -3,9 +3,9 @@
     python -m paper_1804_02883_amd.epd3_timing --n 128 --N 32 --reps 5
 
 Box n^3, FP32 planes (FP64 sums), f_A = 0.3, phibar_P = 0.15, seeded
-potentials 0.2 xi.  An evaluation runs both chains over N contour steps, each
-step 5 FFT launches (the half-step factors ride on the two x passes), plus
-the gauge and partition-function sums and the density kernel.  Prints
+potentials 0.2 xi.  An evaluation runs both chains over N contour steps in
+2N + 1 FFT launches (the last convolution of a step and the first of the next
+share one), plus the gauge and partition-function sums and the density kernel.  Prints
 one JSON line: ms per evaluation (events on the stream around `reps`
 evaluations), `value` in site contour steps per second (n^3 sites x 2N
 steps), and the HBM roofline of the FFT kernel: the mean algorithmic bytes
@@ -31,15 +31,17 @@ def measure(n=128, N=32, reps=5, precision=1):
     d.close()
     sites = n ** 3
     es = 4 if precision else 8
-    # per FFT launch: the complex plane in and out (16 B per site in FP32); the two
-    # x passes of a contour step read or write q, wA, wB (12 B) in place of one
-    # complex plane, so a step's 5 launches move 2 * 20 + 3 * 16 B per site (FP32)
-    alg = sites * es * (2 * 5 + 3 * 4) / 5
+    # planes per FFT launch, both chains: the first reads wA, wB and writes a
+    # factor plane and the scratch plane (8), a shared one reads scratch and
+    # factor and writes q and scratch (8), the last reads scratch and factor and
+    # writes q (6), the y passes between read and write the scratch (4):
+    # (12 N + 6) planes in 2 N + 1 launches
+    alg = sites * es * 6
     avg = fft_ms / fft_launches
     achieved = alg / (avg * 1e-3) / 1e9
     return dict(workload=f"densities3d_{n}^3_N{N}", precision="f32" if precision else "f64", ms_per_eval=ms,
                 value=sites * 2 * N / (ms * 1e-3), unit="site contour steps/s",
-                launches_per_eval=2 * N * 5 + 2 + 5 * 2 + 1,
+                launches_per_eval=2 * N + 1 + 5 + 1,
                 roofline=dict(bound="hbm", kernel="p3_fft", achieved=achieved, peak=8000.0, unit="GB/s",
                               frac=achieved / 8000.0, algorithmic_bytes_per_launch=alg, avg_launch_us=avg * 1e3,
                               traffic=None))
