@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "epdlb.h"
+#include "host_io.hpp"
 #include "kernels.hpp"
 #include "nn.hpp"
 #include "obs.hpp"
@@ -55,6 +56,32 @@ int fail(int code, const std::string& msg) {
     int r_ = (expr);       \
     if (r_ != EPDLB_OK) return r_; \
   } while (0)
+
+// Host FP64 values -> device planes of T, each through conv(index, value);
+// returns when the host array is free again.
+template <typename T, class Conv>
+int host_upload(int device, hipStream_t s, T* dst, const double* src, size_t count, Conv conv) {
+  bool done = false, finite = true;
+  if (count >= kStageMin) HIPCHK(staged_upload(device, s, dst, src, count, conv, &finite, &done));
+  if (done) return EPDLB_OK;
+  std::vector<T> h(count);
+  for (size_t i = 0; i < count; ++i) h[i] = conv(i, src[i]);
+  HIPCHK(hipMemcpyAsync(dst, h.data(), count * sizeof(T), hipMemcpyHostToDevice, s));
+  HIPCHK(hipStreamSynchronize(s));
+  return EPDLB_OK;
+}
+// Device planes of T -> host FP64 values through conv(index, value).
+template <typename T, class Conv>
+int host_download(int device, hipStream_t s, double* dst, const T* src, size_t count, Conv conv) {
+  bool done = false;
+  if (count >= kStageMin) HIPCHK(staged_download(device, s, dst, src, count, conv, &done));
+  if (done) return EPDLB_OK;
+  std::vector<T> h(count);
+  HIPCHK(hipMemcpyAsync(h.data(), src, count * sizeof(T), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  for (size_t i = 0; i < count; ++i) dst[i] = conv(i, h[i]);
+  return EPDLB_OK;
+}
 
 bool is_pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 
@@ -199,6 +226,7 @@ struct epdlb_ctx {
   double* cg_host = nullptr;
   epdlb_cg_info cg_last{};
   int64_t cg_totals[4] = {0, 0, 0, 0};  // inversions, iterations, evaluations, unconverged
+  StageUser io;  // large host transfers share the process's pinned rings
   // offsets are taken modulo 2^64 so that buffers outside the arena (the
   // inversion's scratch) can stand in for arena buffers in a stage
   template <typename T> T* ptr(size_t off) const {
@@ -1183,22 +1211,14 @@ std::string tune_key(const epdlb_ctx* c, int fam) {
 // ---------------------------------------------------------------------------
 template <typename T>
 int upload_t(epdlb_ctx* c, size_t off, const double* src, size_t count) {
-  std::vector<T> tmp(count);
-  for (size_t i = 0; i < count; ++i) tmp[i] = T(src[i]);
-  HIPCHK(hipMemcpyAsync(c->base + off, tmp.data(), count * sizeof(T), hipMemcpyHostToDevice, c->stream));
-  HIPCHK(hipStreamSynchronize(c->stream));
-  return EPDLB_OK;
+  return host_upload(c->device, c->stream, c->ptr<T>(off), src, count, [](size_t, double v) { return T(v); });
 }
 int upload(epdlb_ctx* c, size_t off, const double* src, size_t count) {
   return c->p.precision == 0 ? upload_t<double>(c, off, src, count) : upload_t<float>(c, off, src, count);
 }
 template <typename T>
 int download_t(epdlb_ctx* c, size_t off, double* dst, size_t count) {
-  std::vector<T> tmp(count);
-  HIPCHK(hipMemcpyAsync(tmp.data(), c->base + off, count * sizeof(T), hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(hipStreamSynchronize(c->stream));
-  for (size_t i = 0; i < count; ++i) dst[i] = double(tmp[i]);
-  return EPDLB_OK;
+  return host_download(c->device, c->stream, dst, c->ptr<const T>(off), count, [](size_t, T v) { return double(v); });
 }
 int download(epdlb_ctx* c, size_t off, double* dst, size_t count) {
   return c->p.precision == 0 ? download_t<double>(c, off, dst, count) : download_t<float>(c, off, dst, count);
@@ -1285,36 +1305,46 @@ int upload_populations(epdlb_ctx* c, size_t off, const double* f) {
 }
 
 // LB of replica r at f^eq(rho = 1, u_init); u_init the analytic
-// reverse-Poiseuille profile, into the current population buffer.
+// reverse-Poiseuille profile, into the current population buffer.  The state
+// varies along y only: the rows' values go up (the partial-sum slots hold them)
+// and a kernel spreads them over the 12 planes.
 int init_lb(epdlb_ctx* c, int r) {
   const epdlb_params& p = c->rp[r];
-  const size_t n = size_t(p.nx) * p.ny;
-  std::vector<double> ux(p.ny, 0.0);
-  if (p.init_flow) {
-    const double F0 = g_lattice(p);
-    const double nu = lb_nu(p);
-    const double Ly = p.ny;
-    for (int y = 0; y < p.ny; ++y) {
-      const double Y = y + 0.5 - Ly / 2;
-      ux[y] = -(F0 / (2 * nu)) * Y * (std::fabs(Y) - Ly / 2);
-    }
-  }
+  const size_t ny = size_t(p.ny);
   static const int cx[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
-  std::vector<double> f(9 * n), u(2 * n, 0.0), rho(n, 1.0);
-  for (int y = 0; y < p.ny; ++y)
-    for (int x = 0; x < p.nx; ++x) {
-      const size_t i = size_t(y) * p.nx + x;
-      const double vx = ux[y];
-      u[i] = vx;
-      for (int k = 0; k < 9; ++k) {
-        const double cu = cx[k] * vx;
-        f[k * n + i] = kW9[k] * (1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * vx * vx);
-      }
+  std::vector<double> rows(kLbRowPlanes * ny, 0.0);
+  for (int y = 0; y < p.ny; ++y) {
+    double vx = 0.0;
+    if (p.init_flow) {
+      const double F0 = g_lattice(p);
+      const double nu = lb_nu(p);
+      const double Ly = p.ny;
+      const double Y = y + 0.5 - Ly / 2;
+      vx = -(F0 / (2 * nu)) * Y * (std::fabs(Y) - Ly / 2);
     }
+    for (int k = 0; k < 9; ++k) {
+      const double cu = cx[k] * vx;
+      const double f = kW9[k] * (1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * vx * vx);
+      rows[size_t(k) * ny + size_t(y)] = f - kW9[k];
+    }
+    rows[9 * ny + size_t(y)] = vx;
+    rows[11 * ny + size_t(y)] = 1.0;
+  }
+  static_assert(kLbRowPlanes * 1024 <= 4 * 4096, "the rows of the tallest grid fit the partial-sum slots");
   const size_t o = c->roff(r);
-  CHK(upload_populations(c, o + c->L.fstar[c->fcur], f.data()));
-  CHK(upload(c, o + c->L.u, u.data(), u.size()));
-  CHK(upload(c, o + c->L.rho, rho.data(), rho.size()));
+  double* dev = c->ptr<double>(o + c->L.partials);
+  HIPCHK(hipMemcpyAsync(dev, rows.data(), rows.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
+  const long n = long(p.nx) * p.ny;
+  const dim3 grid(unsigned((n + 255) / 256), kLbRowPlanes), blk(256);
+  const size_t f = o + c->L.fstar[c->fcur], u = o + c->L.u, rho = o + c->L.rho;
+  if (p.precision == 0)
+    launch_k(k_lb_rows<double>, grid, blk, 0, c->stream, (const double*)dev, p.nx, p.ny, c->ptr<double>(f),
+             c->ptr<double>(u), c->ptr<double>(rho));
+  else
+    launch_k(k_lb_rows<float>, grid, blk, 0, c->stream, (const double*)dev, p.nx, p.ny, c->ptr<float>(f),
+             c->ptr<float>(u), c->ptr<float>(rho));
+  HIPCHK(hipGetLastError());
+  HIPCHK(hipStreamSynchronize(c->stream));
   return EPDLB_OK;
 }
 
@@ -2474,7 +2504,7 @@ void epdlb_destroy(epdlb_ctx* c) {
   if (c->cg_host) (void)hipHostFree(c->cg_host);
   if (c->snap) (void)hipHostFree(c->snap);
   if (c->snap_ev) (void)hipEventDestroy(c->snap_ev);
-  if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
+    if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
   delete c;
 }
 
@@ -3076,6 +3106,7 @@ struct epdlb_lb3 {
   hipStream_t stream = nullptr;
   bool own_stream = false;
   std::vector<hipEvent_t> ev;  // start/stop pairs of epdlb_lb3_profile
+  StageUser io;  // large host transfers share the process's pinned rings
   size_t es() const { return precision ? sizeof(float) : sizeof(double); }
 };
 
@@ -3141,34 +3172,28 @@ int lb3_steps(epdlb_lb3* c, int64_t n, hipEvent_t* ev) {
 }
 
 // Host FP64 values -> device planes in the context's precision.
+template <typename T>
+int lb3_upload_t(epdlb_lb3* c, void* dst, const double* src, size_t count, const double* minus_w) {
+  T* d = static_cast<T*>(dst);
+  if (!minus_w) return host_upload(c->device, c->stream, d, src, count, [](size_t, double v) { return T(v); });
+  const size_t n = size_t(c->n);
+  return host_upload(c->device, c->stream, d, src, count, [=](size_t i, double v) { return T(v - minus_w[i / n]); });
+}
 int lb3_upload(epdlb_lb3* c, void* dst, const double* src, size_t count, const double* minus_w) {
-  if (c->precision) {
-    std::vector<float> h(count);
-    for (size_t i = 0; i < count; ++i) h[i] = float(minus_w ? src[i] - minus_w[i / size_t(c->n)] : src[i]);
-    HIPCHK(hipMemcpyAsync(dst, h.data(), count * sizeof(float), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-  } else {
-    std::vector<double> h(count);
-    for (size_t i = 0; i < count; ++i) h[i] = minus_w ? src[i] - minus_w[i / size_t(c->n)] : src[i];
-    HIPCHK(hipMemcpyAsync(dst, h.data(), count * sizeof(double), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-  }
-  return EPDLB_OK;
+  return c->precision ? lb3_upload_t<float>(c, dst, src, count, minus_w)
+                      : lb3_upload_t<double>(c, dst, src, count, minus_w);
 }
 
+template <typename T>
+int lb3_download_t(epdlb_lb3* c, double* dst, const void* src, size_t count, const double* plus_w) {
+  const T* p = static_cast<const T*>(src);
+  if (!plus_w) return host_download(c->device, c->stream, dst, p, count, [](size_t, T v) { return double(v); });
+  const size_t n = size_t(c->n);
+  return host_download(c->device, c->stream, dst, p, count, [=](size_t i, T v) { return plus_w[i / n] + double(v); });
+}
 int lb3_download(epdlb_lb3* c, double* dst, const void* src, size_t count, const double* plus_w) {
-  if (c->precision) {
-    std::vector<float> h(count);
-    HIPCHK(hipMemcpyAsync(h.data(), src, count * sizeof(float), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    for (size_t i = 0; i < count; ++i) dst[i] = plus_w ? plus_w[i / size_t(c->n)] + double(h[i]) : double(h[i]);
-  } else {
-    std::vector<double> h(count);
-    HIPCHK(hipMemcpyAsync(h.data(), src, count * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    for (size_t i = 0; i < count; ++i) dst[i] = plus_w ? plus_w[i / size_t(c->n)] + h[i] : h[i];
-  }
-  return EPDLB_OK;
+  return c->precision ? lb3_download_t<float>(c, dst, src, count, plus_w)
+                      : lb3_download_t<double>(c, dst, src, count, plus_w);
 }
 
 bool all_finite(const double* v, size_t count) {
@@ -3356,7 +3381,7 @@ void epdlb_lb3_destroy(epdlb_lb3* c) {
   if (!c) return;
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
-  if (c->mem) (void)hipFree(c->mem);
+    if (c->mem) (void)hipFree(c->mem);
   if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
   delete c;
 }
@@ -3390,6 +3415,7 @@ struct epdlb_epd3 {
   std::vector<hipEvent_t> ev;  // start/stop pairs of the timed FFT launches (epdlb_epd3_profile)
   size_t ev_used = 0;          // pairs armed in the current evaluation; 0 when not profiling
   bool profiling = false;
+  StageUser io;  // large host transfers share the process's pinned rings
   hipStream_t stream = nullptr;
   bool own_stream = false;
   size_t es() const { return precision ? sizeof(float) : sizeof(double); }
@@ -3691,26 +3717,31 @@ int epdlb_epd3_create(int32_t nx, int32_t ny, int32_t nz, int32_t n_contour, dou
   return EPDLB_OK;
 }
 
+namespace {
+
+// Potentials in, densities out.  Large inputs are checked while they are
+// converted, into the planes of the densities: only accepted ones become the
+// context's potentials.
+template <typename T> int epd3_call(epdlb_epd3* c, const double* omega, double* phi) {
+  const size_t count = 3 * size_t(c->n);
+  auto in = [](size_t, double v) { return T(v); };
+  bool done = false, finite = true;
+  if (count >= kStageMin) HIPCHK(staged_upload(c->device, c->stream, static_cast<T*>(c->phi), omega, count, in, &finite, &done));
+  if (done && finite) std::swap(c->w, c->phi);
+  if (!done) finite = all_finite(omega, count);
+  if (!finite) return fail(EPDLB_EINVAL, "non-finite potential");
+  if (!done) CHK(host_upload(c->device, c->stream, static_cast<T*>(c->w), omega, count, in));
+  CHK(p3_densities<T>(c));
+  return host_download(c->device, c->stream, phi, static_cast<const T*>(c->phi), count,
+                       [](size_t, T v) { return double(v); });
+}
+
+}  // namespace
+
 int epdlb_epd3_densities(epdlb_epd3* c, const double* omega, double* phi, double* Q_P, double* Q_S) {
   if (!c || !omega || !phi) return fail(EPDLB_EINVAL, "NULL argument");
-  const size_t n = size_t(c->n);
-  if (!all_finite(omega, 3 * n)) return fail(EPDLB_EINVAL, "non-finite potential");
   HIPCHK(hipSetDevice(c->device));
-  if (c->precision) {
-    std::vector<float> h(3 * n);
-    for (size_t i = 0; i < 3 * n; ++i) h[i] = float(omega[i]);
-    HIPCHK(hipMemcpyAsync(c->w, h.data(), h.size() * sizeof(float), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    CHK(p3_densities<float>(c));
-    HIPCHK(hipMemcpyAsync(h.data(), c->phi, h.size() * sizeof(float), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    for (size_t i = 0; i < 3 * n; ++i) phi[i] = h[i];
-  } else {
-    HIPCHK(hipMemcpyAsync(c->w, omega, 3 * n * sizeof(double), hipMemcpyHostToDevice, c->stream));
-    CHK(p3_densities<double>(c));
-    HIPCHK(hipMemcpyAsync(phi, c->phi, 3 * n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-  }
+  CHK(c->precision ? epd3_call<float>(c, omega, phi) : epd3_call<double>(c, omega, phi));
   double s[8];
   HIPCHK(hipMemcpyAsync(s, c->sums, sizeof(s), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
@@ -3776,7 +3807,7 @@ void epdlb_epd3_destroy(epdlb_epd3* c) {
   if (!c) return;
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
-  if (c->mem) (void)hipFree(c->mem);
+    if (c->mem) (void)hipFree(c->mem);
   if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
   delete c;
 }

@@ -1014,6 +1014,18 @@ __device__ __forceinline__ void lb_collide(const LbArgs<T>& P, long i, const T (
   P.u[P.n + i] = uy;
 }
 
+// An LB state that varies along y only: rows[p * ny + y] over the rows of plane
+// p = blockIdx.y, the 9 populations, then u (2), then rho.
+constexpr int kLbRowPlanes = 12;
+template <typename T>
+__global__ void __launch_bounds__(256) k_lb_rows(const double* rows, int nx, int ny, T* f, T* u, T* rho) {
+  const long n = long(nx) * ny, i = long(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int p = blockIdx.y;
+  if (i >= n) return;
+  T* d = p < 9 ? f + p * n : (p < 11 ? u + (p - 9) * n : rho);
+  d[i] = T(rows[p * ny + int(i / nx)]);
+}
+
 template <typename T, bool MRT>
 __global__ void __launch_bounds__(256) k_lb(LbArgs<T> P) {
   P.shift(long(blockIdx.z) * P.rs);
