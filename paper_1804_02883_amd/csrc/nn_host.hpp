@@ -123,17 +123,29 @@ hipError_t conv_out(const nn::OutArgs<T>& a, hipStream_t s, int* nblocks) {
   return hipGetLastError();
 }
 
-template <int CI, int CO, int TH>
-hipError_t conv_wgrad(nn::WgradArgs a, int nsamples, hipStream_t s, int* nblocks) {
-  a.tiles_per_sample = (a.nx / nn::kTW) * (a.ny / TH);
+// Partial weight gradients of layer l; *nblocks receives their number.
+hipError_t conv_wgrad(nn::WgradArgs a, int l, int nsamples, hipStream_t s, int* nblocks) {
+  a.tiles_per_sample = (a.nx / nn::kTW) * (a.ny / nn::kWgradTH);
   a.ntiles = a.tiles_per_sample * nsamples;
-  const int d = a.d;
-  const size_t lds = size_t(nn::kTW + 2 * d) * (TH + 2 * d) * (CI + 8) * 2 + size_t(TH) * nn::kTW * (CO + 8) * 2;
-  auto k = nn::k_conv_wgrad<CI, CO, TH>;
-  hipError_t e = prep_lds(k, lds);
-  if (e != hipSuccess) return e;
-  *nblocks = std::min(a.ntiles, kWgradMaxBlocks);
-  launch_k(k, dim3(*nblocks), dim3(576), lds, s, a);
+  // one workgroup per CU: each writes a partial of the whole layer
+  *nblocks = std::min(a.ntiles, std::min(device_cus(), kWgradMaxBlocks));
+  if (l == 0) {
+    launch_k(nn::k_wgrad_in, dim3(*nblocks), dim3(nn::kWgradEdgeThreads), 0, s, a);
+  } else if (l == 3) {
+    launch_k(nn::k_wgrad_out, dim3(*nblocks), dim3(nn::kWgradEdgeThreads), 0, s, a);
+  } else {
+    auto run = [&](auto k, int d) {
+      const int hw = (nn::kTW + 2 * d + 7) / 8 * 8;
+      const size_t lds = size_t(hw * (nn::kWgradTH + 2 * d) + nn::kWgradSites) * 128;
+      const hipError_t e = prep_lds(k, lds);
+      if (e != hipSuccess) return e;
+      launch_k(k, dim3(*nblocks), dim3(nn::kWgradThreads), lds, s, a);
+      return hipSuccess;
+    };
+    static_assert(nn::dil_of(1) == 2 && nn::dil_of(2) == 4 && nn::dil_of(3) == 8, "dilations of the kernels");
+    const hipError_t e = l == 1 ? run(nn::k_wgrad64<2>, 2) : run(nn::k_wgrad64<4>, 4);
+    if (e != hipSuccess) return e;
+  }
   return hipGetLastError();
 }
 
@@ -142,15 +154,15 @@ hipError_t wgrad_reduce(const float* part, const float* partb, int nblocks, int 
   a.part = part;
   a.partb = partb;
   a.nblocks = nblocks;
-  a.CIs = fwd_cis(l);
-  a.COs = l == 3 ? nn::kXC : nn::kHid;
+  a.CIs = nn::cin_of(l);
+  a.COs = nn::cout_of(l);
   a.in64 = l > 0 ? 1 : 0;
   a.out64 = l < 3 ? 1 : 0;
   a.cil = nn::cin_of(l);
   a.col = nn::cout_of(l);
   a.grad = grad;
   const int total = 9 * a.cil * a.col + a.col;
-  hipLaunchKernelGGL(nn::k_wgrad_reduce, dim3((total + 255) / 256), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(nn::k_wgrad_reduce, dim3((total + 63) / 64), dim3(nn::kWredThreads), 0, s, a);
   return hipGetLastError();
 }
 
@@ -463,8 +475,7 @@ int nn_backward(epdlb_nn* t, int count) {
   wa.slots = nullptr;
   wa.g = t->g4;
   wa.g_bs = n * nn::kXC;
-  wa.d = nn::dil_of(3);
-  HIPCHK((conv_wgrad<nn::kHid, nn::kXC, 4>(wa, count, t->stream, &nb)));
+  HIPCHK(conv_wgrad(wa, 3, count, t->stream, &nb));
   HIPCHK(wgrad_reduce(t->wpart, t->wpartb, nb, 3, t->g + o.W[3], t->stream));
   // layers 2 and 1
   __bf16* gin = t->gb[0];
@@ -481,8 +492,7 @@ int nn_backward(epdlb_nn* t, int count) {
     wa.a_bs = n * nn::kHid;
     wa.g = gin;
     wa.g_bs = n * nn::kHid;
-    wa.d = nn::dil_of(l);
-    HIPCHK((conv_wgrad<nn::kHid, nn::kHid, 8>(wa, count, t->stream, &nb)));
+    HIPCHK(conv_wgrad(wa, l, count, t->stream, &nb));
     HIPCHK(wgrad_reduce(t->wpart, t->wpartb, nb, l, t->g + o.W[l], t->stream));
     std::swap(gin, gout);
   }
@@ -492,8 +502,7 @@ int nn_backward(epdlb_nn* t, int count) {
   wa.slots = t->slots;
   wa.g = gin;
   wa.g_bs = n * nn::kHid;
-  wa.d = 1;
-  HIPCHK((conv_wgrad<nn::kXC, nn::kHid, 8>(wa, count, t->stream, &nb)));
+  HIPCHK(conv_wgrad(wa, 0, count, t->stream, &nb));
   HIPCHK(wgrad_reduce(t->wpart, t->wpartb, nb, 0, t->g + o.W[0], t->stream));
   return EPDLB_OK;
 }
