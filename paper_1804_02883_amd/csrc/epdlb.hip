@@ -101,7 +101,7 @@ double unit_open0(uint64_t bits) { return (double((bits >> 11)) + 1.0) * 0x1.0p-
 // ---------------------------------------------------------------------------
 struct Layout {
   size_t omega[2], phi, stilde, S, q[2], tmp, spec, F, fstar[2], rho, u, boltz;
-  size_t mult_x, mult_y, tw_x, tw_y, wnA, wnB, scal, partials, counters;
+  size_t mult_x, mult_y, tw_x, tw_y, ker_x, ker_y, wnA, wnB, scal, partials, counters;
   // surrogate mode only (density_mode 1)
   size_t nn_act[2], nn_w, nn_frag, nn_phin, nn_corr, nn_proj;
   size_t total;
@@ -141,6 +141,8 @@ Layout make_layout(const epdlb_params& p) {
   L.mult_y = take(size_t(p.ny) * es);
   L.tw_x = take(size_t(p.nx) * 2 * es);
   L.tw_y = take(size_t(p.ny) * 2 * es);
+  L.ker_x = take(size_t(p.nx) * es);
+  L.ker_y = take(size_t(p.ny) * es);
   L.wnA = take(size_t(N + 1) * es);
   L.wnB = take(size_t(N + 1) * es);
   L.scal = take(kNumScal * sizeof(double));
@@ -239,10 +241,10 @@ namespace {
 
 int nn_after_seed(epdlb_ctx* c);
 
-enum Kind { K_STATS, K_ADVECT, K_FINISH, K_PROP_ROW, K_PROP_COL, K_DENSITY, K_FROW_FWD, K_FCOL,
+enum Kind { K_STATS, K_ADVECT, K_FINISH, K_PROP_RES, K_PROP_ROW, K_PROP_COL, K_DENSITY, K_FROW_FWD, K_FCOL,
             K_FROW_INV, K_LB, K_NN_CONV0, K_NN_CONV, K_NN_OUT, K_NN_NORM, K_NN_RESET, K_ADVECT_ONLY, K_CG,
             K_FINV_LB, K_NORM_FROW, K_NUM };
-const char* const kKindName[K_NUM] = {"field_stats", "advect_update", "finish_stats",
+const char* const kKindName[K_NUM] = {"field_stats", "advect_update", "finish_stats",  "prop_resident",
                                       "prop_row",    "prop_col",      "density",       "force_row_fwd",
                                       "force_col",   "force_row_inv", "lb",            "nn_conv0",
                                       "nn_conv",     "nn_out",        "nn_norm",       "nn_reset",
@@ -632,10 +634,50 @@ UpdArgs<T> make_upd_args(epdlb_ctx* c, bool flow) {
   return a;
 }
 
+// Grids whose chain propagators run resident on one CU (k_prop_res).  Its cost
+// per contour step is its matrix-pipe time, 32 (FP32) or 64 (FP64) cycles per
+// MFMA of a wave times the waves that share a SIMD; a launch per step costs 4-6
+// us.  Measured per step, resident against the passes: 64 x 64 FP32 (4,096
+// cycles) 2.8 against 4.1-5.3 us, 128 x 32 (5,120) 2.9 against 4.3, 32 x 32 FP64
+// (2,048) 1.8 against 3.9-5.7, 64 x 32 FP64 (3,072) 2.2 against 4.2; beyond, 64 x
+// 64 FP64 (8,192) 5.3 against 4.4, 128 x 64 FP32 (12,288) 6.3 against 4.6.
+constexpr int kResMaxCycles = 5120;
+constexpr int res_cycles(int nx, int ny, int precision) {
+  const int kx = nx / 16, ky = ny / 16;
+  return (ky * kx + ky * ky) * 4 * (precision == 0 ? 64 : 32) * (kx > 4 ? (kx + 3) / 4 : 1);
+}
+bool resident(const epdlb_params& p) { return res_cycles(p.nx, p.ny, p.precision) <= kResMaxCycles; }
+
+template <typename T, int LX, int LY> hipError_t launch_prop_res(const ResArgs<T>& a, int nrep, hipStream_t s) {
+  if constexpr (res_cycles(LX, LY, sizeof(T) == 8 ? 0 : 1) <= kResMaxCycles) {
+    launch_k((k_prop_res<T, LX, LY>), dim3(2, 1, nrep), dim3(4 * LX), 0, s, a);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
+}
+template <typename T, int LX> hipError_t prop_res_y(int ny, const ResArgs<T>& a, int nrep, hipStream_t s) {
+  switch (ny) {
+    case 16: return launch_prop_res<T, LX, 16>(a, nrep, s);
+    case 32: return launch_prop_res<T, LX, 32>(a, nrep, s);
+    case 64: return launch_prop_res<T, LX, 64>(a, nrep, s);
+  }
+  return hipErrorInvalidValue;
+}
+template <typename T> hipError_t prop_res(int nx, int ny, const ResArgs<T>& a, int nrep, hipStream_t s) {
+  switch (nx) {
+    case 32: return prop_res_y<T, 32>(ny, a, nrep, s);
+    case 64: return prop_res_y<T, 64>(ny, a, nrep, s);
+    case 128: return prop_res_y<T, 128>(ny, a, nrep, s);
+  }
+  return hipErrorInvalidValue;
+}
+
 // flow = false: mu and the omega update at the stored fields without
 // convection (used after the Phi -> omega inversion, which convects first).
+// finish = false: the field statistics stay partial sums, for a stage_densities
+// that follows and is told so.
 template <typename T>
-int stage_advect_update(epdlb_ctx* c, bool flow = true) {
+int stage_advect_update(epdlb_ctx* c, bool flow = true, bool finish = true) {
   const epdlb_params& p = c->p;
   const long n = long(p.nx) * p.ny;
   UpdArgs<T> a = make_upd_args<T>(c, flow);
@@ -644,7 +686,7 @@ int stage_advect_update(epdlb_ctx* c, bool flow = true) {
     launch_k((k_advect_update<T>), dim3(p.nx / kTX, p.ny / kTY, c->nrep), dim3(kTX * kTY), 0, c->stream, a);
   }
   HIPCHK(hipGetLastError());
-  {
+  if (finish) {
     ProfScope ps(c, K_FINISH);
     launch_k(k_finish_stats, dim3(1, 1, c->nrep), dim3(256), 0, c->stream, a.partials,
              (p.nx / kTX) * (p.ny / kTY), c->ptr<double>(c->L.scal), n, p.dx * p.dx, long(c->rstride));
@@ -684,12 +726,18 @@ PropArgs<T> make_prop_args(epdlb_ctx* c) {
   return a;
 }
 
+// Slots of the two chains' sums from k_prop_res: past those of k_advect_update,
+// which its other workgroup may still be reading.
+constexpr size_t kResPartial = 8192;
+
+// unfinished: the field statistics are k_advect_update's partial sums.
 template <typename T>
-int stage_densities(epdlb_ctx* c, bool with_S) {
+int stage_densities(epdlb_ctx* c, bool with_S, bool unfinished = false) {
   const epdlb_params& p = c->p;
   const int N = p.n_contour;
   const long n = long(p.nx) * p.ny;
   PropArgs<T> a = make_prop_args<T>(c);
+  const bool res = resident(p);
   auto launch = [&](bool row) -> int {
     if (row) {
       a.nf = c->sh_row.nf;
@@ -702,35 +750,58 @@ int stage_densities(epdlb_ctx* c, bool with_S) {
     }
     return EPDLB_OK;
   };
-  // step 0 starts with its x convolution of E(step 0); that first pass also
-  // writes the half-step factor planes the later passes read
-  // segment A fractions (uniform over the replicas of a launch)
-  const std::vector<double> segA = segment_fractions(p);
-  auto seg = [&](int chain, int step) { return T(segA[chain == 0 ? step : N - 1 - step]); };
-  a.a = 0;
-  a.first = 1;
-  a.mid = a.second = a.last = 0;
-  for (int ch = 0; ch < 2; ++ch) a.frac[ch][0] = a.frac[ch][1] = seg(ch, 0);
-  CHK(launch(true));
-  // boundary a -> a+1: last convolution of step a and first of step a+1
-  // (y-oriented after an even step, x-oriented after an odd one)
-  a.first = 0;
-  a.mid = 1;
-  for (int s = 0; s < N; ++s) {
-    a.a = s;
-    a.second = s + 1 < N;
-    a.last = s + 1 == N;
-    for (int ch = 0; ch < 2; ++ch) {
-      a.frac[ch][0] = seg(ch, s);
-      a.frac[ch][1] = s + 1 < N ? seg(ch, s + 1) : seg(ch, s);
+  if (res) {
+    ResArgs<T> r;
+    r.wA = a.wA;
+    r.wB = a.wB;
+    r.scal = a.scal;
+    r.q[0] = a.q[0];
+    r.q[1] = a.q[1];
+    r.cx = c->ptr<T>(c->L.ker_x);
+    r.cy = c->ptr<T>(c->L.ker_y);
+    r.partials = a.partials + kResPartial;
+    r.plane = n;
+    r.N = N;
+    r.fAN = p.f_A * N;
+    r.stat = a.partials;
+    r.nstat = unfinished ? (p.nx / kTX) * (p.ny / kTY) : 0;
+    r.scal_out = c->ptr<double>(c->L.scal);
+    r.dA = p.dx * p.dx;
+    r.rs = long(c->rstride);
+    ProfScope ps(c, K_PROP_RES);
+    HIPCHK(prop_res<T>(p.nx, p.ny, r, c->nrep, c->stream));
+  } else {
+    // step 0 starts with its x convolution of E(step 0); that first pass also
+    // writes the half-step factor planes the later passes read
+    // segment A fractions (uniform over the replicas of a launch)
+    const std::vector<double> segA = segment_fractions(p);
+    auto seg = [&](int chain, int step) { return T(segA[chain == 0 ? step : N - 1 - step]); };
+    a.a = 0;
+    a.first = 1;
+    a.mid = a.second = a.last = 0;
+    for (int ch = 0; ch < 2; ++ch) a.frac[ch][0] = a.frac[ch][1] = seg(ch, 0);
+    CHK(launch(true));
+    // boundary a -> a+1: last convolution of step a and first of step a+1
+    // (y-oriented after an even step, x-oriented after an odd one)
+    a.first = 0;
+    a.mid = 1;
+    for (int s = 0; s < N; ++s) {
+      a.a = s;
+      a.second = s + 1 < N;
+      a.last = s + 1 == N;
+      for (int ch = 0; ch < 2; ++ch) {
+        a.frac[ch][0] = seg(ch, s);
+        a.frac[ch][1] = s + 1 < N ? seg(ch, s + 1) : seg(ch, s);
+      }
+      CHK(launch(s % 2 == 1));
     }
-    CHK(launch(s % 2 == 1));
   }
   DensArgs<T> d;
-  d.qpart = a.partials;
+  d.qpart = res ? a.partials + kResPartial : a.partials;
   // partial slots of the final propagator launch (x-oriented if N-1 is odd)
-  d.nqpart = ((N - 1) % 2 == 1) ? (p.ny / 2 + c->sh_row.nf - 1) / c->sh_row.nf
-                                : (p.nx / 2 + c->sh_col.nf - 1) / c->sh_col.nf;
+  d.nqpart = res ? 1
+                 : ((N - 1) % 2 == 1) ? (p.ny / 2 + c->sh_row.nf - 1) / c->sh_row.nf
+                                      : (p.nx / 2 + c->sh_col.nf - 1) / c->sh_col.nf;
   d.dA = p.dx * p.dx;
   d.scal_out = c->ptr<double>(c->L.scal);
   d.q[0] = a.q[0];
@@ -1097,6 +1168,17 @@ int run_stage(epdlb_ctx* c, int stage) {
   return c->p.precision == 0 ? run_stage_t<double>(c, stage) : run_stage_t<float>(c, stage);
 }
 
+// The first two stages of a step together: a resident propagator finishes the
+// field statistics itself.
+template <typename T> int advect_densities_t(epdlb_ctx* c) {
+  const bool fold = resident(c->p) && !c->p.cg_invert;
+  CHK(c->p.cg_invert ? stage_advect_cg<T>(c) : stage_advect_update<T>(c, true, !fold));
+  return stage_densities<T>(c, true, fold);
+}
+int run_advect_densities(epdlb_ctx* c) {
+  return c->p.precision == 0 ? advect_densities_t<double>(c) : advect_densities_t<float>(c);
+}
+
 // ---------------------------------------------------------------------------
 // Autotuner for the FFT pass launch shapes (values per lane R, transforms per
 // block nf).  A candidate is timed as a captured graph of `reps` back-to-back
@@ -1260,7 +1342,27 @@ int upload_tables(epdlb_ctx* c) {
       out[2 * e + 1] = -std::sin(ang);
     }
   };
-  std::vector<double> mx, my, tx, ty;
+  // The kernel in real space, c_d = (1/L) sum_k exp(-R_G^2 k^2 ds) cos(k d).  The
+  // rounding of its values must not add up over the steps as a loss or gain of
+  // the total: the smallest one, at d = L/2, takes what they miss of 1.
+  auto ker = [&](int L, std::vector<double>& out) {
+    out.assign(L, 0.0);
+    std::vector<double> m;
+    mult(L, m);
+    for (int d = 0; d < L; ++d)
+      for (int k = 0; k < L; ++k) out[d] += m[k] * std::cos(2.0 * M_PI * double((long(k) * d) % L) / L);
+    double miss = 1.0;
+    for (double& v : out) {
+      if (p.precision) v = double(float(v));
+      miss -= v;
+    }
+    out[L / 2] += miss;
+  };
+  std::vector<double> mx, my, tx, ty, kx, ky;
+  if (resident(p)) {
+    ker(p.nx, kx);
+    ker(p.ny, ky);
+  }
   mult(p.nx, mx);
   mult(p.ny, my);
   tw(p.nx, tx);
@@ -1269,6 +1371,10 @@ int upload_tables(epdlb_ctx* c) {
     const size_t o = c->roff(r);
     CHK(upload(c, o + c->L.mult_x, mx.data(), mx.size()));
     CHK(upload(c, o + c->L.mult_y, my.data(), my.size()));
+    if (!kx.empty()) {
+      CHK(upload(c, o + c->L.ker_x, kx.data(), kx.size()));
+      CHK(upload(c, o + c->L.ker_y, ky.data(), ky.size()));
+    }
     CHK(upload(c, o + c->L.tw_x, tx.data(), tx.size()));
     CHK(upload(c, o + c->L.tw_y, ty.data(), ty.size()));
     // node weights: trapezoid over each segment, split by its A fraction
@@ -1390,7 +1496,7 @@ int get_graph(epdlb_ctx* c, int steps, int kind, hipGraphExec_t* out) {
   int r = EPDLB_OK;
   for (int s = 0; s < steps && r == EPDLB_OK; ++s) {
     if (kind == 0) {
-      for (int st = EPDLB_STAGE_ADVECT_UPDATE; st <= EPDLB_STAGE_DENSITIES && r == EPDLB_OK; ++st) r = run_stage(c, st);
+      r = run_advect_densities(c);
       if (r == EPDLB_OK) r = run_force_lb(c);
     } else {
       r = run_sur_step(c, kind);
@@ -1563,7 +1669,7 @@ int batch_graph(epdlb_batch* b, int steps, hipGraphExec_t* out) {
     epdlb_ctx* c = b->groups[i];
     if (hipStreamWaitEvent(b->fork[i], b->ev_fork, 0) != hipSuccess) r = fail(EPDLB_EHIP, "fork wait");
     for (int st = 0; st < steps && r == EPDLB_OK; ++st) {
-      for (int k = EPDLB_STAGE_ADVECT_UPDATE; k <= EPDLB_STAGE_DENSITIES && r == EPDLB_OK; ++k) r = run_stage(c, k);
+      r = run_advect_densities(c);
       if (r == EPDLB_OK) r = run_force_lb(c);
     }
     if (r == EPDLB_OK && hipEventRecord(b->ev_join[i], b->fork[i]) != hipSuccess) r = fail(EPDLB_EHIP, "join");
@@ -1861,7 +1967,7 @@ int epdlb_step(epdlb_ctx* c, int64_t n) {
     return EPDLB_OK;
   }
   for (int64_t s = 0; s < n; ++s) {
-    for (int st = EPDLB_STAGE_ADVECT_UPDATE; st <= EPDLB_STAGE_DENSITIES; ++st) CHK(run_stage(c, st));
+    CHK(run_advect_densities(c));
     CHK(run_force_lb(c));
     ++c->nstep;
   }
@@ -2616,8 +2722,7 @@ int epdlb_batch_step(epdlb_batch* b, int64_t n) {
       for (auto* c : b->groups) {
         hipStream_t own = c->stream;
         c->stream = b->stream;
-        int r = EPDLB_OK;
-        for (int k = EPDLB_STAGE_ADVECT_UPDATE; k <= EPDLB_STAGE_DENSITIES && r == EPDLB_OK; ++k) r = run_stage(c, k);
+        int r = run_advect_densities(c);
         if (r == EPDLB_OK) r = run_force_lb(c);
         c->stream = own;
         CHK(r);

@@ -112,6 +112,15 @@ __device__ __forceinline__ void sum_partials(const double* partials, int nslots,
   block_sum<NV>(acc, red);
 }
 
+// The scalars of the field statistics from their sums.
+__device__ __forceinline__ void finish_stats(double* scal, const double (&acc)[4], long n, double dA) {
+  scal[kGaugeS] = scal[kMeanS];  // the constant the exponentials were taken with
+  scal[kMeanA] = acc[0] / double(n);
+  scal[kMeanB] = acc[1] / double(n);
+  scal[kMeanS] = acc[2] / double(n);
+  scal[kQS] = acc[3] * dA;
+}
+
 // Finishes the field statistics: partials of (sum w_A, sum w_B, sum w_S,
 // sum exp(-(w_S - gauge))) -> means, Q_S and the gauge it used.  One block.
 __global__ void __launch_bounds__(256) k_finish_stats(const double* partials, int nslots, double* scal,
@@ -121,13 +130,7 @@ __global__ void __launch_bounds__(256) k_finish_stats(const double* partials, in
   scal = sh(scal, long(blockIdx.z) * rs);
   double acc[4];
   sum_partials<4>(partials, nslots, acc, red);
-  if (threadIdx.x == 0) {
-    scal[kGaugeS] = scal[kMeanS];  // the constant the exponentials were taken with
-    scal[kMeanA] = acc[0] / double(n);
-    scal[kMeanB] = acc[1] / double(n);
-    scal[kMeanS] = acc[2] / double(n);
-    scal[kQS] = acc[3] * dA;
-  }
+  if (threadIdx.x == 0) finish_stats(scal, acc, n, dA);
 }
 
 // ---------------------------------------------------------------------------
@@ -421,6 +424,186 @@ __global__ void __launch_bounds__(512) k_prop_col(PropArgs<T> P) {
 }
 
 // ---------------------------------------------------------------------------
+// Chain propagators of a small grid in one launch: one workgroup per chain
+// (blockIdx.x) and replica keeps its plane on one CU for all N contour steps.
+// At these sizes a convolution is cheapest as a product with the circulant
+// matrix of the kernel's real-space values (c_x, c_y): MFMA in the planes' own
+// precision, no exchanges.  Wave w owns the 16 columns from 16 w, all rows:
+//   x:  D = Q C_x, rows of Q from LDS (16-byte reads), C_x in registers;
+//   y:  C_y D, where the output layout of the first product is the operand
+//       layout of the second up to the order of the summed rows, which the
+//       registers of C_y follow: no data moves between the two;
+// then x E, store q_{a+1}, x E of the next step, back to LDS (two buffers, one
+// barrier per step).  A circulant matrix takes L/4 registers of a wave: the
+// element at (row, column) depends on their difference only.
+// What bounds it: the matrix pipes of one CU (64 x 64 FP32: 128 MFMAs of 32
+// cycles per wave and step, 1.7 of the 2.8 us measured; 32 x 32 FP64 1.8 us),
+// where a launch per step took 4.1-5.7 us whatever the size.
+// ---------------------------------------------------------------------------
+template <typename T> struct Mfma16;
+template <> struct Mfma16<float> {
+  typedef float acc __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ acc mma(float a, float b, acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  // row of register i in lane group g (16 lanes)
+  static __device__ __forceinline__ int row(int g, int i) { return 4 * g + i; }
+};
+template <> struct Mfma16<double> {
+  typedef double acc __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ acc mma(double a, double b, acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int g, int i) { return 4 * i + g; }
+};
+
+template <typename T> struct ResArgs {
+  const T* wA;
+  const T* wB;
+  const double* scal;  // kMeanA, kMeanB
+  T* q[2];             // q_1..q_N of chain c
+  const T* cx;         // kernel of the x convolution at distance 0..nx-1
+  const T* cy;
+  double* partials;    // sum of q_N of chain c at [c]
+  long plane;
+  int N;
+  double fAN;          // f_A N: segment j has A fraction clip(f_A N - j, 0, 1)
+  // nstat > 0: the field statistics of k_advect_update are still partial sums
+  // (at most 64 slots here, so that the sums are k_finish_stats' bit for bit);
+  // both workgroups add them, chain 0's writes the scalars
+  const double* stat;
+  int nstat;
+  double* scal_out;
+  double dA;
+  long rs;
+  __device__ void shift(long o) {
+    wA = sh(wA, o), wB = sh(wB, o), scal = sh(scal, o), q[0] = sh(q[0], o), q[1] = sh(q[1], o);
+    cx = sh(cx, o), cy = sh(cy, o), partials = sh(partials, o), stat = sh(stat, o), scal_out = sh(scal_out, o);
+  }
+};
+
+template <typename T, int LX, int LY>
+__global__ void __launch_bounds__(4 * LX) k_prop_res(ResArgs<T> P) {
+  using M = Mfma16<T>;
+  using A4 = typename M::acc;
+  constexpr int KX = LX / 16, KY = LY / 16;
+  constexpr int S = LX + (sizeof(T) == 4 ? 4 : 2);  // row stride: 16 rows' 16-byte reads on distinct banks
+  __shared__ __attribute__((aligned(16))) T buf[2][LY * S];
+  __shared__ double red[16 * 4];
+  __shared__ double mean_s[2];
+  P.shift(long(blockIdx.z) * P.rs);
+  const int c = blockIdx.x;
+  const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+  const int x0 = (threadIdx.x >> 6) * 16;
+  if (P.nstat > 0) {
+    double acc[4];
+    sum_partials<4>(P.stat, P.nstat, acc, red);
+    if (threadIdx.x == 0) {
+      mean_s[0] = acc[0] / double(P.plane);
+      mean_s[1] = acc[1] / double(P.plane);
+      if (c == 0) finish_stats(P.scal_out, acc, P.plane, P.dA);
+    }
+  } else if (threadIdx.x == 0) {
+    mean_s[0] = P.scal[kMeanA];
+    mean_s[1] = P.scal[kMeanB];
+  }
+  __syncthreads();
+  const T ca = T(mean_s[0]), cb = T(mean_s[1]);
+  T cx[KX][4], cy[KY][4];
+#pragma unroll
+  for (int k = 0; k < KX; ++k)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) cx[k][i] = P.cx[(x0 + n - (16 * k + 4 * g + i)) & (LX - 1)];
+#pragma unroll
+  for (int k = 0; k < KY; ++k)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) cy[k][i] = P.cy[(16 * k + n - M::row(g, i)) & (LY - 1)];
+  // this lane's sites: column x0 + n, rows 16 m + row(g, i)
+  auto site = [&](int m, int i) { return (16 * m + M::row(g, i)) * LX + x0 + n; };
+  T ea[KY][4], eb[KY][4];
+#pragma unroll
+  for (int m = 0; m < KY; ++m)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const T wa = P.wA[site(m, i)], wb = P.wB[site(m, i)];
+      ea[m][i] = boltz(wa, wb, T(1), ca, cb);
+      eb[m][i] = boltz(wa, wb, T(0), ca, cb);
+    }
+  auto frac = [&](int step) {
+    const double v = P.fAN - double(c == 0 ? step : P.N - 1 - step);
+    return T(v < 0.0 ? 0.0 : (v > 1.0 ? 1.0 : v));
+  };
+  auto times_e = [&](A4 (&v)[KY], T fr) {
+#pragma unroll
+    for (int m = 0; m < KY; ++m)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (fr == T(1)) v[m][i] *= ea[m][i];
+        else if (fr == T(0)) v[m][i] *= eb[m][i];
+        else v[m][i] *= boltz(P.wA[site(m, i)], P.wB[site(m, i)], fr, ca, cb);
+      }
+  };
+  auto to_lds = [&](T* b, const A4 (&v)[KY]) {
+#pragma unroll
+    for (int m = 0; m < KY; ++m)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) b[(16 * m + M::row(g, i)) * S + x0 + n] = v[m][i];
+  };
+  A4 v[KY];
+#pragma unroll
+  for (int m = 0; m < KY; ++m)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[m][i] = T(1);
+  times_e(v, frac(0));
+  to_lds(buf[0], v);
+  double qsum = 0.0;
+  for (int s = 0; s < P.N; ++s) {
+    __syncthreads();
+    const T* b = buf[s & 1];
+    // the KY products of a step of the sum are independent: their MFMAs go back to back
+    A4 d[KY];
+#pragma unroll
+    for (int m = 0; m < KY; ++m) d[m] = A4{T(0), T(0), T(0), T(0)};
+#pragma unroll
+    for (int k = 0; k < KX; ++k) {
+      A4 a[KY];
+#pragma unroll
+      for (int m = 0; m < KY; ++m) a[m] = *reinterpret_cast<const A4*>(b + (16 * m + n) * S + 16 * k + 4 * g);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int m = 0; m < KY; ++m) d[m] = M::mma(a[m][i], cx[k][i], d[m]);
+    }
+#pragma unroll
+    for (int m = 0; m < KY; ++m) v[m] = A4{T(0), T(0), T(0), T(0)};
+#pragma unroll
+    for (int k = 0; k < KY; ++k)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int m = 0; m < KY; ++m) v[m] = M::mma(cy[(m - k + KY) % KY][i], d[k][i], v[m]);
+    const T fr = frac(s);
+    times_e(v, fr);
+    T* qo = (c == 0 ? P.q[0] : P.q[1]) + long(s) * P.plane;
+#pragma unroll
+    for (int m = 0; m < KY; ++m)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) qo[site(m, i)] = v[m][i];
+    if (s + 1 < P.N) {
+      times_e(v, frac(s + 1));
+      to_lds(buf[(s + 1) & 1], v);
+    } else {
+#pragma unroll
+      for (int m = 0; m < KY; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) qsum += double(v[m][i]);
+    }
+  }
+  double r[1] = {qsum};
+  block_partial<1>(r, red, P.partials, c);
+}
+
+// ---------------------------------------------------------------------------
 // Densities (contour integrals, solvent) and S = sum_I Phi_I/D_I - S~.
 // ---------------------------------------------------------------------------
 template <typename T> struct DensArgs {
@@ -484,10 +667,25 @@ __global__ void __launch_bounds__(256) k_density(DensArgs<T> P) {
     sA += P.wnA[0] * prod;
     sB += P.wnB[0] * prod;
   }
-  for (int j = 1; j < N; ++j) {
-    const T prod = P.q[0][long(j - 1) * P.n + i] * P.q[1][long(N - j - 1) * P.n + i];
-    sA += P.wnA[j] * prod;
-    sB += P.wnB[j] * prod;
+  // eight nodes' loads in flight: where the grid is small a load's latency per
+  // node is what the kernel takes
+  for (int j0 = 1; j0 < N; j0 += 8) {
+    T f[8], b[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int j = min(j0 + k, N - 1);
+      f[k] = P.q[0][long(j - 1) * P.n + i];
+      b[k] = P.q[1][long(N - j - 1) * P.n + i];
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int j = j0 + k;
+      if (j < N) {
+        const T prod = f[k] * b[k];
+        sA += P.wnA[j] * prod;
+        sB += P.wnB[j] * prod;
+      }
+    }
   }
   {
     const T prod = P.q[0][long(N - 1) * P.n + i];
