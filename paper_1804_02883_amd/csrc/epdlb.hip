@@ -362,19 +362,19 @@ hipError_t prep_lds(K kernel, size_t bytes) {
 
 template <typename T, int L, int R>
 constexpr bool fft_ok() {
-  return (R == 8 || ((R == 16 || R == 4 || R == 2) && sizeof(T) == 4)) && L >= R;
+  return (R == 8 || R == 4 || ((R == 16 || R == 2) && sizeof(T) == 4)) && L >= R;
 }
 constexpr int kMaxColThreads = 512;
 
-template <typename T, int L, int R>
+template <typename T, int L, int R, bool FIRST>
 hipError_t launch_prop_row_r(const PropArgs<T>& a, hipStream_t s) {
   if constexpr (fft_ok<T, L, R>()) {
     using V = LdsView<T, L, R, true, 1>;
     const size_t lds = 2 * size_t(V::size_elems(a.nf)) * sizeof(T);
-    hipError_t e = prep_lds(k_prop_row<T, L, R>, lds);
+    hipError_t e = prep_lds(k_prop_row<T, L, R, FIRST>, lds);
     if (e != hipSuccess) return e;
     const int tiles = (a.ny / 2 + a.nf - 1) / a.nf;
-    launch_k((k_prop_row<T, L, R>), dim3(tiles, 2, a.nrep), dim3(a.nf * (L / R)), lds, s, a);
+    launch_k((k_prop_row<T, L, R, FIRST>), dim3(tiles, 2, a.nrep), dim3(a.nf * (L / R)), lds, s, a);
     return hipGetLastError();
   }
   return hipErrorInvalidValue;
@@ -382,18 +382,26 @@ hipError_t launch_prop_row_r(const PropArgs<T>& a, hipStream_t s) {
 template <typename T, int L>
 hipError_t launch_prop_row(const PropArgs<T>& a, int R, hipStream_t s) {
   switch (R) {
-    case 16: return launch_prop_row_r<T, L, 16>(a, s);
-    case 4: return launch_prop_row_r<T, L, 4>(a, s);
-    case 2: return launch_prop_row_r<T, L, 2>(a, s);
+    case 16: return launch_prop_row_r<T, L, 16, false>(a, s);
+    case 4: return launch_prop_row_r<T, L, 4, false>(a, s);
+    case 2: return launch_prop_row_r<T, L, 2, false>(a, s);
   }
-  return launch_prop_row_r<T, L, 8>(a, s);
+  return launch_prop_row_r<T, L, 8, false>(a, s);
+}
+// The first pass of a propagation; it comes with R = 4 and 8.
+template <typename T, int L>
+hipError_t launch_prop_first(const PropArgs<T>& a, int R, hipStream_t s) {
+  PropArgs<T> f = a;
+  const int r = R >= 8 ? 8 : 4;
+  f.nf = clampi(64 * r / L, 1, a.ny / 2);
+  return r == 8 ? launch_prop_row_r<T, L, 8, true>(f, s) : launch_prop_row_r<T, L, 4, true>(f, s);
 }
 
 template <typename T, int L, int R, int NF>
 hipError_t launch_prop_col_rn(const PropArgs<T>& a, hipStream_t s) {
   if constexpr (fft_ok<T, L, R>() && NF * (L / R) <= kMaxColThreads && (sizeof(T) == 4 || NF == 4)) {
-    using V = LdsView<T, L, R, false, NF>;
-    const size_t lds = 2 * size_t(V::size_elems(NF)) * sizeof(T);
+    const size_t elems = col_mapped<L, R>() ? NF * ColView<T, L, R>::kLen : LdsView<T, L, R, false, NF>::size_elems(NF);
+    const size_t lds = elems * sizeof(T2<T>);
     hipError_t e = prep_lds(k_prop_col<T, L, R, NF>, lds);
     if (e != hipSuccess) return e;
     const int tiles = (a.nx / 2 + NF - 1) / NF;
@@ -560,6 +568,9 @@ hipError_t launch_norm_force_row(const ForceArgs<T>& a, const nn::NormArgs<T>& q
 template <typename T> hipError_t prop_row(int L, int R, const PropArgs<T>& a, hipStream_t s) {
   EPDLB_SWITCH_L(L, launch_prop_row, T, a, R, s)
 }
+template <typename T> hipError_t prop_first(int L, int R, const PropArgs<T>& a, hipStream_t s) {
+  EPDLB_SWITCH_L(L, launch_prop_first, T, a, R, s)
+}
 template <typename T> hipError_t prop_col(int L, int R, const PropArgs<T>& a, hipStream_t s) {
   EPDLB_SWITCH_L(L, launch_prop_col, T, a, R, s)
 }
@@ -717,9 +728,12 @@ PropArgs<T> make_prop_args(epdlb_ctx* c) {
   a.ny = p.ny;
   a.plane = n;
   a.partials = c->ptr<double>(c->L.partials);
+  a.EJ = nullptr;
+  a.E[0][0] = a.E[0][1] = a.EA;
+  a.E[1][0] = a.E[1][1] = a.EB;
   a.a = 0;
-  a.first = a.mid = a.second = a.last = 0;
-  a.frac[0][0] = a.frac[0][1] = a.frac[1][0] = a.frac[1][1] = T(1);
+  a.second = a.last = 0;
+  a.frac[0] = a.frac[1] = a.fracJ = T(1);
   a.nf = 1;
   a.nrep = c->nrep;
   a.rs = long(c->rstride);
@@ -772,26 +786,32 @@ int stage_densities(epdlb_ctx* c, bool with_S, bool unfinished = false) {
     HIPCHK(prop_res<T>(p.nx, p.ny, r, c->nrep, c->stream));
   } else {
     // step 0 starts with its x convolution of E(step 0); that first pass also
-    // writes the half-step factor planes the later passes read
+    // writes the half-step factor planes the later passes read: A's, B's and the
+    // junction segment's (into the force spectrum's plane, unused until the force)
     // segment A fractions (uniform over the replicas of a launch)
     const std::vector<double> segA = segment_fractions(p);
-    auto seg = [&](int chain, int step) { return T(segA[chain == 0 ? step : N - 1 - step]); };
-    a.a = 0;
-    a.first = 1;
-    a.mid = a.second = a.last = 0;
-    for (int ch = 0; ch < 2; ++ch) a.frac[ch][0] = a.frac[ch][1] = seg(ch, 0);
-    CHK(launch(true));
+    auto frac = [&](int chain, int step) { return T(segA[chain == 0 ? step : N - 1 - step]); };
+    T* junction = c->ptr<T>(c->L.spec);
+    for (int j = 0; j < N; ++j)
+      if (T(segA[j]) != T(0) && T(segA[j]) != T(1)) {
+        a.EJ = junction;
+        a.fracJ = T(segA[j]);
+      }
+    auto plane_of = [&](T fr) { return (const T*)(fr == T(1) ? a.EA : fr == T(0) ? a.EB : junction); };
+    for (int ch = 0; ch < 2; ++ch) a.frac[ch] = frac(ch, 0);
+    {
+      ProfScope ps(c, K_PROP_ROW);
+      HIPCHK(prop_first<T>(p.nx, c->sh_row.R, a, c->stream));
+    }
     // boundary a -> a+1: last convolution of step a and first of step a+1
     // (y-oriented after an even step, x-oriented after an odd one)
-    a.first = 0;
-    a.mid = 1;
     for (int s = 0; s < N; ++s) {
       a.a = s;
       a.second = s + 1 < N;
       a.last = s + 1 == N;
       for (int ch = 0; ch < 2; ++ch) {
-        a.frac[ch][0] = seg(ch, s);
-        a.frac[ch][1] = s + 1 < N ? seg(ch, s + 1) : seg(ch, s);
+        a.E[ch][0] = plane_of(frac(ch, s));
+        a.E[ch][1] = s + 1 < N ? plane_of(frac(ch, s + 1)) : a.E[ch][0];
       }
       CHK(launch(s % 2 == 1));
     }
@@ -1203,7 +1223,7 @@ hipError_t launch_family(epdlb_ctx* c, int fam, int R, int nf, hipStream_t s) {
   if (fam == F_PROP_ROW || fam == F_PROP_COL) {
     PropArgs<T> a = make_prop_args<T>(c);
     a.a = 0;  // fused boundary kernel: writes q_1 and the scratch plane
-    a.mid = a.second = 1;
+    a.second = 1;
     a.nf = nf;
     return fam == F_PROP_ROW ? prop_row<T>(p.nx, R, a, s) : prop_col<T>(p.ny, R, a, s);
   }
@@ -1522,20 +1542,28 @@ int get_graph(epdlb_ctx* c, int steps, int kind, hipGraphExec_t* out) {
   return EPDLB_OK;
 }
 
-// Default launch shapes (R = 8 values per lane).  Row passes: nf transforms of
-// L/R lanes per block (<= 256 lanes); column passes: NF transforms
-// interleaved, NF*L/R <= 512 lanes, NF = 8 where it fits.
+// Default launch shapes.  A pass is latency-bound (a chain of loads, FFT passes
+// and stores with one or two waves per SIMD), so more lanes with fewer values
+// each win until the exchanges cost more: R = 4, except for lengths where R = 8
+// makes a transform one wave (rows of 512) or halves 512-lane barriers (columns
+// of 512 and more).  Rows: one wave per block, two of 512; columns: 4 pairs, which
+// gives twice the blocks of 8 and still 32-byte segments.  Measured per pass
+// (us), R = 8 with 256-lane rows and 8 column pairs -> these: 256 x 256 rows 5.2 ->
+// 3.5, columns 6.2 -> 4.8; 1024 x 512 rows 8.7 -> 7.7, columns 8.8 -> 8.2; 512 x 512
+// rows 5.6 -> 5.2, columns 8.2 -> 6.8; 128 x 128 4.8 -> 3.4 and 5.1 -> 4.0; FP64
+// 256 x 128 8.1 -> 4.0 and 5.1 -> 4.5.
+// A surrogate context keeps R = 8: its network reads the potentials rounded to
+// BF16, so a transform that rounds differently moves whole BF16 steps and a run
+// would not repeat (2.6e-5 of the potentials after 50 steps of 512 x 512).
 void default_shapes(epdlb_ctx* c) {
   const epdlb_params* p = &c->p;
-  auto row_nf = [&](int L, int transforms) {
-    const int tl = L / 8;
-    return clampi(256 / tl, 1, transforms);
-  };
-  auto col_nf = [&](int L) { return (L / 8) * 8 <= 512 ? 8 : 4; };
-  c->sh_row = {8, row_nf(p->nx, p->ny / 2)};
-  c->sh_col = {8, p->precision == 0 ? 4 : col_nf(p->ny)};
-  c->sh_frow = {8, row_nf(p->nx, p->ny)};
-  c->sh_fcol = {8, p->precision == 0 ? 4 : col_nf(p->ny)};
+  const bool keep = p->density_mode == 1;
+  const int row_r = keep || p->nx == 512 ? 8 : 4, col_r = keep || p->ny >= 512 ? 8 : 4;
+  auto row_nf = [&](int transforms) { return clampi((row_r == 8 && p->nx >= 512 ? 128 : 64) * row_r / p->nx, 1, transforms); };
+  c->sh_row = {row_r, row_nf(p->ny / 2)};
+  c->sh_col = {col_r, 4};
+  c->sh_frow = {row_r, row_nf(p->ny)};
+  c->sh_fcol = {col_r, 4};
 }
 
 int check_finite(epdlb_ctx* c) {
@@ -2494,7 +2522,7 @@ int epdlb_autotune(epdlb_ctx* c, int32_t reps, const char* cache_path) {
     epdlb_ctx::Shape best_sh = family_shape(c, fam);
     const int Rs[4] = {2, 4, 8, 16};
     for (int R : Rs) {
-      if (R != 8 && !fp32) continue;
+      if (R != 8 && R != 4 && !fp32) continue;
       if (row) {
         for (int nf = 1; nf * (L / R) <= 512 && nf <= transforms; nf *= 2) {
           const double us = time_candidate(c, fam, R, nf, reps);

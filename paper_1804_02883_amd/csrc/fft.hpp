@@ -159,6 +159,20 @@ template <int L, int R> struct Plan {
   __device__ static __forceinline__ int skew_il(int i) { return i ^ (((i >> 2) ^ (i >> 3)) & 3); }
 };
 
+// Ordering of the LDS accesses of an exchange: between the waves of a block, or
+// within a wave, whose LDS operations complete in order, so that only the
+// compiler has to keep them so.
+enum Sync : int { kSyncNone, kSyncWave, kSyncBlock };
+template <Sync S> __device__ __forceinline__ void lds_sync() {
+  if constexpr (S == kSyncWave) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else if constexpr (S == kSyncBlock) {
+    __syncthreads();
+  }
+}
+
 // LDS view of one transform: complex element i (real and imaginary part
 // side by side, one 64-/128-bit access each).
 //  * CONTIG:      transform f occupies [f*LP, (f+1)*LP)
@@ -173,6 +187,8 @@ struct LdsView {
     if constexpr (CONTIG) return f * Plan<L, R>::LP + Plan<L, R>::skew(i);
     else return f + NF * Plan<L, R>::skew_il(i);
   }
+  // A transform's lanes all lie in one wave: its exchanges need no barrier.
+  static constexpr Sync kSync = CONTIG && L / R <= 64 ? kSyncWave : kSyncBlock;
   // complex elements needed for nf transforms
   __host__ __device__ static constexpr int size_elems(int nf) {
     return CONTIG ? Plan<L, R>::LP * nf : NF * Plan<L, R>::LP;
@@ -184,7 +200,9 @@ struct LdsView {
 // out[(jj/Ns)*Ns*r + jj%Ns + q*Ns].  FROM_REG / TO_REG: the pass reads /
 // leaves its data in the lane's registers (natural layout j + T*m).  P: the
 // pass's place in its direction; tw: its twiddles (Twiddles or TwTables).
-template <typename T, int L, int R, int r, int Ns, int SIGN, bool FROM_REG, bool TO_REG, int P, class V, class TW>
+// BEFORE / AFTER order the write against earlier readers and later ones.
+template <typename T, int L, int R, int r, int Ns, int SIGN, bool FROM_REG, bool TO_REG, int P, Sync BEFORE, Sync AFTER,
+          class V, class TW>
 __device__ __forceinline__ void stockham_pass(T* re, T* im, int j, const V& lds, const TW& tw) {
   constexpr int TL = L / R;
   constexpr int SUB = R / r;
@@ -248,7 +266,7 @@ __device__ __forceinline__ void stockham_pass(T* re, T* im, int j, const V& lds,
         im[s + q * SUB] = vi[s * r + q];
       }
   } else {
-    __syncthreads();  // previous readers of the buffer are done
+    lds_sync<BEFORE>();  // previous readers of the buffer are done
 #pragma unroll
     for (int s = 0; s < SUB; ++s) {
       const int jj = j + TL * s;
@@ -261,7 +279,7 @@ __device__ __forceinline__ void stockham_pass(T* re, T* im, int j, const V& lds,
         lds.buf[lds.at(base + q * Ns)] = v;
       }
     }
-    __syncthreads();
+    lds_sync<AFTER>();
   }
 }
 
@@ -342,9 +360,60 @@ template <typename T, int L, int R, int P, bool FWD, class V, class TW>
 __device__ __forceinline__ void run_passes(T* re, T* im, int j, const V& lds, const TW& t) {
   using PI = PassInfo<L, R, P, FWD>;
   constexpr int S = Plan<L, R>::S;
-  stockham_pass<T, L, R, PI::r, PI::Ns, FWD ? -1 : +1, P == 0, P == S - 1, P>(re, im, j, lds, t);
+  stockham_pass<T, L, R, PI::r, PI::Ns, FWD ? -1 : +1, P == 0, P == S - 1, P, V::kSync, V::kSync>(re, im,
+                                                                                                        j, lds, t);
   if constexpr (P + 1 < S) run_passes<T, L, R, P + 1, FWD>(re, im, j, lds, t);
 }
+
+// ---------------------------------------------------------------------------
+// Columns: a block's NF transforms are loaded and stored interleaved lane by
+// lane (thread = f + NF j), which the memory accesses need, but transformed one
+// after the other (thread = j + TL f), with TL <= 64 so that a transform lies in
+// one wave: the passes between the first exchange of a forward and the last of
+// an inverse transform need no barrier, three per convolution instead of 4 (S -
+// 1).  The mapping changes in those two exchanges, through the LDS buffer.
+// ---------------------------------------------------------------------------
+template <typename T, int L, int R>
+struct ColView {
+  T2<T>* buf;
+  int f;
+  // transforms 1 element apart mod 16, so that the interleaved accesses of 4 or 8
+  // transforms fall on distinct banks beside the skewed contiguous ones
+  static constexpr int kLen = L + 1;
+  __device__ __forceinline__ int at(int i) const { return f * kLen + Plan<L, R>::skew(i); }
+};
+template <typename T, int L, int R> struct ColMap {
+  ColView<T, L, R> mem, wave;  // the transforms of the two mappings
+  int jm, jw;                  // and the lanes within them
+};
+template <typename T, int L, int R, int P, class TW>
+__device__ __forceinline__ void col_forward(T* re, T* im, const ColMap<T, L, R>& c, const TW& t) {
+  using PI = PassInfo<L, R, P, true>;
+  constexpr int S = Plan<L, R>::S;
+  if constexpr (P == 0) {
+    stockham_pass<T, L, R, PI::r, PI::Ns, -1, true, false, P, kSyncBlock, kSyncBlock>(re, im, c.jm, c.mem, t);
+  } else {
+    stockham_pass<T, L, R, PI::r, PI::Ns, -1, false, P == S - 1, P, kSyncWave, kSyncWave>(re, im, c.jw, c.wave, t);
+  }
+  if constexpr (P + 1 < S) col_forward<T, L, R, P + 1>(re, im, c, t);
+}
+template <typename T, int L, int R, int P, class TW>
+__device__ __forceinline__ void col_inverse(T* re, T* im, const ColMap<T, L, R>& c, const TW& t) {
+  using PI = PassInfo<L, R, P, false>;
+  constexpr int S = Plan<L, R>::S;
+  if constexpr (P == S - 1) {
+    stockham_pass<T, L, R, PI::r, PI::Ns, +1, false, true, P, kSyncNone, kSyncNone>(re, im, c.jm, c.mem, t);
+  } else {
+    stockham_pass<T, L, R, PI::r, PI::Ns, +1, P == 0, false, P, kSyncWave, P == S - 2 ? kSyncBlock : kSyncWave>(
+        re, im, c.jw, c.wave, t);
+    col_inverse<T, L, R, P + 1>(re, im, c, t);
+  }
+}
+// Shapes that use it: a transform in one wave, R <= 4.  Measured per pass, one
+// mapping throughout -> this: 128 x 128 4.4 -> 4.0 us, 256 x 256 4.9 -> 4.8, FP64
+// 256 x 128 4.9 -> 4.5 (R = 4); 512 columns at R = 8 6.8 -> 7.0, FP64 128 at R = 8
+// 5.1 -> 5.4 (half the barriers to save, more registers).
+template <int L, int R> constexpr bool col_mapped() { return L / R <= 64 && R <= 4 && Plan<L, R>::S > 1; }
 
 // Twiddle sets for a forward and an inverse transform (load both before the
 // data arrives; `tw` holds W_L^e = exp(-2 pi i e/L)).
@@ -355,6 +424,26 @@ __device__ __forceinline__ void load_fwd_twiddles(Twiddles<T, L, R>& t, int j, c
 template <typename T, int L, int R>
 __device__ __forceinline__ void load_inv_twiddles(Twiddles<T, L, R>& t, int j, const T2<T>* tw) {
   load_twiddles<T, L, R, 0, false>(t, j, tw);
+}
+
+// The inverse set of the column mapping: the last pass runs in the memory mapping.
+template <typename T, int L, int R, int P>
+__device__ __forceinline__ void load_twiddles_pass(Twiddles<T, L, R>& t, int j, const T2<T>* __restrict__ tw) {
+  using PI = PassInfo<L, R, P, false>;
+  constexpr int r = PI::r, Ns = PI::Ns, TL = L / R;
+  if constexpr (Ns > 1) {
+#pragma unroll
+    for (int s = 0; s < R / r; ++s) {
+      const int k = (j + TL * s) & (Ns - 1);
+      t.w1[P][s] = tw[k * (L / (Ns * r))];
+      t.wh[P][s] = tw[k * (r / 2) * (L / (Ns * r))];
+    }
+  }
+}
+template <typename T, int L, int R>
+__device__ __forceinline__ void load_col_inv_twiddles(Twiddles<T, L, R>& t, int jw, int jm, const T2<T>* tw) {
+  load_twiddles<T, L, R, 0, false>(t, jw, tw);
+  load_twiddles_pass<T, L, R, Plan<L, R>::S - 1>(t, jm, tw);
 }
 
 // x (time, lane layout j + T*m) -> X (frequency, same layout), radices

@@ -142,10 +142,12 @@ __global__ void __launch_bounds__(256) k_finish_stats(const double* partials, in
 // launch (blockIdx.y = chain; 0 forward, 1 backward).
 // ---------------------------------------------------------------------------
 template <typename T> struct PropArgs {
-  const T* wA;
+  const T* wA;            // first pass
   const T* wB;
-  const T* EA;            // exp(-(w_A - c_A)/2), written once per propagation
-  const T* EB;            // exp(-(w_B - c_B)/2)
+  T* EA;                  // first pass: exp(-(w_A - c_A)/2), written for the later ones
+  T* EB;                  // exp(-(w_B - c_B)/2)
+  T* EJ;                  // the same of the junction segment (A fraction fracJ); nullptr: none
+  const T* E[2][2];       // factor plane of chain c at step a (+0/+1): EA, EB or EJ
   const double* scal;     // kMeanA, kMeanB: gauge constants
   T* q[2];                // q_1..q_N of chain c at q[c] + (j-1)*plane
   T* tmp;                 // 2 planes (per chain): data between the two convolutions of a step
@@ -156,17 +158,19 @@ template <typename T> struct PropArgs {
   int nx, ny;
   long plane;
   int a;                  // contour step finished by the first convolution
-  int first;              // input is E(step 0) (q_0 = 1) instead of tmp
-  int mid;                // after convolution 1: x E(step a), store q_{a+1}
   int second;             // then x E(step a+1), convolution 2, store tmp
-  int last;               // with mid: partial sums of q_N for Q_P
-  T frac[2][2];           // A fraction of the segment used by chain c at step a (+0/+1)
+  int last;               // partial sums of q_N for Q_P
+  T frac[2];              // first pass: A fraction of chain c's segment at step 0
+  T fracJ;
   double* partials;       // last: per-block sums of q_N, chain c at [c*gridDim.x]
   int nf;                 // transforms per block (row kernels)
   int nrep;               // replicas in the launch (gridDim.z)
   long rs;                // replica stride in bytes
   __device__ void shift(long o) {
     wA = sh(wA, o), wB = sh(wB, o), EA = sh(EA, o), EB = sh(EB, o), scal = sh(scal, o);
+    if (EJ) EJ = sh(EJ, o);
+    for (int c = 0; c < 2; ++c)
+      for (int k = 0; k < 2; ++k) E[c][k] = sh(E[c][k], o);
     q[0] = sh(q[0], o), q[1] = sh(q[1], o), tmp = sh(tmp, o), mult_x = sh(mult_x, o);
     mult_y = sh(mult_y, o), tw_x = sh(tw_x, o), tw_y = sh(tw_y, o);
     partials = sh(partials, o);
@@ -180,27 +184,14 @@ __device__ __forceinline__ T boltz(T wa, T wb, T a, T ca, T cb) {
   return exp(T(-0.5) * x);
 }
 
-// Half-step Boltzmann factor exp(-(w_seg - c_seg)/2) of a segment with A
-// fraction `fr` at flat index i: a plane load for pure A or B segments, the
-// mixed junction segment from the potentials.
-template <typename T>
-__device__ __forceinline__ T efactor(const PropArgs<T>& P, T fr, T ca, T cb, long i) {
-  if (fr == T(1)) return P.EA[i];
-  if (fr == T(0)) return P.EB[i];
-  return boltz(P.wA[i], P.wB[i], fr, ca, cb);
+// Element at a 32-bit byte offset (a plane is below 4 GiB), so that accesses
+// take a scalar base and one offset register.
+template <typename X> __device__ __forceinline__ X ld(const void* base, unsigned off) {
+  return *reinterpret_cast<const X*>(static_cast<const char*>(base) + off);
 }
-template <typename T>
-__device__ __forceinline__ T2<T> efactor2(const PropArgs<T>& P, T fr, T ca, T cb, long i2) {
-  if (fr == T(1)) return reinterpret_cast<const T2<T>*>(P.EA)[i2];
-  if (fr == T(0)) return reinterpret_cast<const T2<T>*>(P.EB)[i2];
-  const T2<T> u = reinterpret_cast<const T2<T>*>(P.wA)[i2];
-  const T2<T> w = reinterpret_cast<const T2<T>*>(P.wB)[i2];
-  T2<T> e;
-  e.x = boltz(u.x, w.x, fr, ca, cb);
-  e.y = boltz(u.y, w.y, fr, ca, cb);
-  return e;
+template <typename X> __device__ __forceinline__ void st(void* base, unsigned off, X v) {
+  *reinterpret_cast<X*>(static_cast<char*>(base) + off) = v;
 }
-
 
 // Convolution with the real, even multiplier g in the lane layout.
 template <typename T, int L, int R, class V>
@@ -215,9 +206,32 @@ __device__ __forceinline__ void convolve(T* re, T* im, int j, const V& lds, cons
   fft_inverse<T, L, R>(re, im, j, lds, twi);
 }
 
+// The same over the columns of a block (ColMap); g in the wave mapping.
+template <typename T, int L, int R>
+__device__ __forceinline__ void convolve_cols(T* re, T* im, const ColMap<T, L, R>& c, const Twiddles<T, L, R>& twf,
+                                              const Twiddles<T, L, R>& twi, const T* g) {
+  col_forward<T, L, R, 0>(re, im, c, twf);
+#pragma unroll
+  for (int m = 0; m < R; ++m) {
+    re[m] *= g[m];
+    im[m] *= g[m];
+  }
+  col_inverse<T, L, R, 0>(re, im, c, twi);
+}
+
 // x-oriented kernel: rows 2rp and 2rp+1 of one chain packed as one complex
 // row (the multiplier is real and even, so the two real rows stay apart).
-template <typename T, int L, int R>
+//
+// The passes are short and latency-bound, so the code path of a launch is kept
+// short and straight: the first pass is an instantiation of its own, the
+// factors come from one plane per step (the junction segment has one too),
+// every load is unconditional (a transform past the end repeats the last one
+// and stores nothing).  With a branch per element that picked the factor's
+// plane or evaluated the junction's, and 64-bit addresses (2,360 instructions
+// in the 256-row pass), a pass took, in alternation with the other kind: 256 x 256
+// 5.5 us, now 4.5; 512 x 512 8.0, now 6.6; 1024 x 512 9.8, now 9.3; 128 x 128 5.1,
+// now 3.9; FP64 256 x 128 6.0, now 4.5 (same shapes, same results bit for bit).
+template <typename T, int L, int R, bool FIRST>
 __global__ void __launch_bounds__(512) k_prop_row(PropArgs<T> P) {
   constexpr int TL = L / R;
   using V = LdsView<T, L, R, true, 1>;
@@ -227,81 +241,78 @@ __global__ void __launch_bounds__(512) k_prop_row(PropArgs<T> P) {
   V lds{reinterpret_cast<T2<T>*>(smem_raw), f};
   P.shift(long(blockIdx.z) * P.rs);
   const int c = blockIdx.y;
-  const int rp = blockIdx.x * P.nf + f;
-  const bool active = rp < P.ny / 2;
-  const long r0 = long(2 * rp) * P.nx, r1 = r0 + P.nx;
-  const T ca = T(P.scal[kMeanA]), cb = T(P.scal[kMeanB]);
-  const T fr0 = c == 0 ? P.frac[0][0] : P.frac[1][0], fr1 = c == 0 ? P.frac[0][1] : P.frac[1][1];
+  const int want = blockIdx.x * P.nf + f, rp = min(want, P.ny / 2 - 1);
+  const bool active = want == rp;
+  const unsigned r0 = (unsigned(2 * rp) * L + j) * sizeof(T), r1 = r0 + L * sizeof(T);
+  constexpr unsigned kStep = TL * sizeof(T);  // element j + TL m lies m steps on
+  T* tmp = P.tmp + c * P.plane;
+  T re[R], im[R], ea[R], eb[R];
+  if constexpr (FIRST) {
+    // the factors from the potentials; the factor planes of the later passes:
+    // A's from the forward chain's blocks, B's from the backward chain's
+    const T ca = T(P.scal[kMeanA]), cb = T(P.scal[kMeanB]);
+    const T fr0 = c == 0 ? P.frac[0] : P.frac[1];
+    T* Ep = c == 0 ? P.EA : P.EB;
+    const T pure = c == 0 ? T(1) : T(0);
+#pragma unroll
+    for (int m = 0; m < R; ++m) {
+      const unsigned o0 = r0 + m * kStep, o1 = r1 + m * kStep;
+      const T wa0 = ld<T>(P.wA, o0), wb0 = ld<T>(P.wB, o0), wa1 = ld<T>(P.wA, o1), wb1 = ld<T>(P.wB, o1);
+      const T p0 = boltz(wa0, wb0, pure, ca, cb), p1 = boltz(wa1, wb1, pure, ca, cb);
+      if (active) {
+        st(Ep, o0, p0);
+        st(Ep, o1, p1);
+        if (c == 0 && P.EJ) {
+          st(P.EJ, o0, boltz(wa0, wb0, P.fracJ, ca, cb));
+          st(P.EJ, o1, boltz(wa1, wb1, P.fracJ, ca, cb));
+        }
+      }
+      re[m] = fr0 == pure ? p0 : boltz(wa0, wb0, fr0, ca, cb);
+      im[m] = fr0 == pure ? p1 : boltz(wa1, wb1, fr0, ca, cb);
+    }
+  } else {
+    const T* E0 = c == 0 ? P.E[0][0] : P.E[1][0];
+#pragma unroll
+    for (int m = 0; m < R; ++m) {
+      re[m] = ld<T>(tmp, r0 + m * kStep);
+      im[m] = ld<T>(tmp, r1 + m * kStep);
+    }
+#pragma unroll
+    for (int m = 0; m < R; ++m) {
+      ea[m] = ld<T>(E0, r0 + m * kStep);
+      eb[m] = ld<T>(E0, r1 + m * kStep);
+    }
+  }
   Twiddles<T, L, R> twf, twi;
   load_fwd_twiddles(twf, j, P.tw_x);
   load_inv_twiddles(twi, j, P.tw_x);
   T g[R];
 #pragma unroll
   for (int m = 0; m < R; ++m) g[m] = P.mult_x[j + TL * m];
-  T* tmp = P.tmp + c * P.plane;
-  // half-step factors of step a (loaded early: they overlap the first convolution)
-  T ea[R], eb[R];
-  if (P.first) {
-    // the first pass takes its factors from the potentials and leaves the
-    // factor planes of the later passes: A's from the forward chain's blocks,
-    // B's from the backward chain's (the same values a separate pass gave)
-    T* Ep = const_cast<T*>(c == 0 ? P.EA : P.EB);
-    const T pure = c == 0 ? T(1) : T(0);
-#pragma unroll
-    for (int m = 0; m < R; ++m) {
-      const int x = j + TL * m;
-      ea[m] = eb[m] = T(0);
-      if (active) {
-        const T wa0 = P.wA[r0 + x], wb0 = P.wB[r0 + x], wa1 = P.wA[r1 + x], wb1 = P.wB[r1 + x];
-        const T p0 = boltz(wa0, wb0, pure, ca, cb), p1 = boltz(wa1, wb1, pure, ca, cb);
-        Ep[r0 + x] = p0;
-        Ep[r1 + x] = p1;
-        ea[m] = fr0 == pure ? p0 : boltz(wa0, wb0, fr0, ca, cb);
-        eb[m] = fr0 == pure ? p1 : boltz(wa1, wb1, fr0, ca, cb);
-      }
-    }
-  } else {
-#pragma unroll
-    for (int m = 0; m < R; ++m) {
-      const int x = j + TL * m;
-      ea[m] = active && P.mid ? efactor(P, fr0, ca, cb, r0 + x) : T(0);
-      eb[m] = active && P.mid ? efactor(P, fr0, ca, cb, r1 + x) : T(0);
-    }
-  }
-  T re[R], im[R];
-#pragma unroll
-  for (int m = 0; m < R; ++m) {
-    const int x = j + TL * m;
-    if (P.first) {
-      re[m] = ea[m];
-      im[m] = eb[m];
-    } else {
-      re[m] = active ? tmp[r0 + x] : T(0);
-      im[m] = active ? tmp[r1 + x] : T(0);
-    }
-  }
   convolve(re, im, j, lds, twf, twi, g);
   double qsum = 0.0;
-  if (P.mid) {
+  if constexpr (!FIRST) {
     T* qo = (c == 0 ? P.q[0] : P.q[1]) + long(P.a) * P.plane;
 #pragma unroll
     for (int m = 0; m < R; ++m) {
-      const int x = j + TL * m;
       re[m] *= ea[m];
       im[m] *= eb[m];
-      if (active) {
-        qo[r0 + x] = re[m];
-        qo[r1 + x] = im[m];
-      }
       qsum += double(re[m]) + double(im[m]);
     }
+    if (active)
+#pragma unroll
+      for (int m = 0; m < R; ++m) {
+        st(qo, r0 + m * kStep, re[m]);
+        st(qo, r1 + m * kStep, im[m]);
+      }
     if (P.second) {
-      if (fr1 != fr0) {
+      const T* E0 = c == 0 ? P.E[0][0] : P.E[1][0];
+      const T* E1 = c == 0 ? P.E[0][1] : P.E[1][1];
+      if (E1 != E0) {
 #pragma unroll
         for (int m = 0; m < R; ++m) {
-          const int x = j + TL * m;
-          ea[m] = active ? efactor(P, fr1, ca, cb, r0 + x) : T(0);
-          eb[m] = active ? efactor(P, fr1, ca, cb, r1 + x) : T(0);
+          ea[m] = ld<T>(E1, r0 + m * kStep);
+          eb[m] = ld<T>(E1, r1 + m * kStep);
         }
       }
 #pragma unroll
@@ -312,16 +323,15 @@ __global__ void __launch_bounds__(512) k_prop_row(PropArgs<T> P) {
       convolve(re, im, j, lds, twf, twi, g);
     }
   }
-  if ((!P.mid || P.second) && active) {
+  if ((FIRST || P.second) && active) {
 #pragma unroll
     for (int m = 0; m < R; ++m) {
-      const int x = j + TL * m;
-      tmp[r0 + x] = re[m];
-      tmp[r1 + x] = im[m];
+      st(tmp, r0 + m * kStep, re[m]);
+      st(tmp, r1 + m * kStep, im[m]);
     }
   }
-  if (P.last) {
-    double v[1] = {qsum};
+  if (!FIRST && P.last) {
+    double v[1] = {active ? qsum : 0.0};
     block_partial<1>(v, red, P.partials + c * gridDim.x, blockIdx.x);
   }
 }
@@ -337,88 +347,79 @@ __global__ void __launch_bounds__(512) k_prop_col(PropArgs<T> P) {
   __shared__ double red[16 * 1];
   const int f = threadIdx.x % NF, j = threadIdx.x / NF;
   V lds{reinterpret_cast<T2<T>*>(smem_raw), f};
+  constexpr bool kMap = col_mapped<L, R>();
+  const int jw = kMap ? int(threadIdx.x) % TL : j;  // the lane within the transform between the exchanges
   P.shift(long(blockIdx.z) * P.rs);
   const int lt = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
   const int c = lt / gridDim.x, tile = lt % gridDim.x;
-  const int cp = tile * NF + f;
-  const bool active = cp < P.nx / 2;
-  const int x0 = 2 * cp;
-  const T ca = T(P.scal[kMeanA]), cb = T(P.scal[kMeanB]);
-  const T fr0 = c == 0 ? P.frac[0][0] : P.frac[1][0], fr1 = c == 0 ? P.frac[0][1] : P.frac[1][1];
-  Twiddles<T, L, R> twf, twi;
-  load_fwd_twiddles(twf, j, P.tw_y);
-  load_inv_twiddles(twi, j, P.tw_y);
-  T g[R];
-#pragma unroll
-  for (int m = 0; m < R; ++m) g[m] = P.mult_y[j + TL * m];
-  T2<T>* tmp2 = reinterpret_cast<T2<T>*>(P.tmp + c * P.plane);
+  const int want = tile * NF + f, cp = min(want, P.nx / 2 - 1);
+  const bool active = want == cp;
+  const unsigned o0 = (unsigned(j) * P.nx + 2 * cp) * sizeof(T), step = unsigned(TL) * P.nx * sizeof(T);
+  T* tmp = P.tmp + c * P.plane;
+  const T* E0 = c == 0 ? P.E[0][0] : P.E[1][0];
+  T re[R], im[R];
   T2<T> e[R];
 #pragma unroll
   for (int m = 0; m < R; ++m) {
-    const long i2 = (long(j + TL * m) * P.nx + x0) >> 1;
-    e[m].x = T(0);
-    e[m].y = T(0);
-    if (active && (P.first || P.mid)) e[m] = efactor2(P, fr0, ca, cb, i2);
+    const T2<T> v = ld<T2<T>>(tmp, o0 + m * step);
+    re[m] = v.x;
+    im[m] = v.y;
   }
-  T re[R], im[R];
 #pragma unroll
-  for (int m = 0; m < R; ++m) {
-    const long i2 = (long(j + TL * m) * P.nx + x0) >> 1;
-    if (P.first) {
-      re[m] = e[m].x;
-      im[m] = e[m].y;
+  for (int m = 0; m < R; ++m) e[m] = ld<T2<T>>(E0, o0 + m * step);
+  Twiddles<T, L, R> twf, twi;
+  load_fwd_twiddles(twf, jw, P.tw_y);
+  if constexpr (kMap)
+    load_col_inv_twiddles(twi, jw, j, P.tw_y);
+  else
+    load_inv_twiddles(twi, j, P.tw_y);
+  T g[R];
+#pragma unroll
+  for (int m = 0; m < R; ++m) g[m] = P.mult_y[jw + TL * m];
+  auto conv = [&] {
+    if constexpr (kMap) {
+      T2<T>* buf = reinterpret_cast<T2<T>*>(smem_raw);
+      const ColMap<T, L, R> cm{{buf, f}, {buf, int(threadIdx.x) / TL}, j, jw};
+      convolve_cols<T, L, R>(re, im, cm, twf, twi, g);
     } else {
-      T2<T> v;
-      v.x = T(0);
-      v.y = T(0);
-      if (active) v = tmp2[i2];
-      re[m] = v.x;
-      im[m] = v.y;
-    }
-  }
-  convolve(re, im, j, lds, twf, twi, g);
-  double qsum = 0.0;
-  if (P.mid) {
-    T2<T>* qo = reinterpret_cast<T2<T>*>((c == 0 ? P.q[0] : P.q[1]) + long(P.a) * P.plane);
-#pragma unroll
-    for (int m = 0; m < R; ++m) {
-      const long i2 = (long(j + TL * m) * P.nx + x0) >> 1;
-      re[m] *= e[m].x;
-      im[m] *= e[m].y;
-      T2<T> o;
-      o.x = re[m];
-      o.y = im[m];
-      if (active) qo[i2] = o;
-      qsum += double(o.x) + double(o.y);
-    }
-    if (P.second) {
-      if (fr1 != fr0) {
-#pragma unroll
-        for (int m = 0; m < R; ++m) {
-          const long i2 = (long(j + TL * m) * P.nx + x0) >> 1;
-          if (active) e[m] = efactor2(P, fr1, ca, cb, i2);
-        }
-      }
-#pragma unroll
-      for (int m = 0; m < R; ++m) {
-        re[m] *= e[m].x;
-        im[m] *= e[m].y;
-      }
       convolve(re, im, j, lds, twf, twi, g);
     }
+  };
+  conv();
+  double qsum = 0.0;
+  T* qo = (c == 0 ? P.q[0] : P.q[1]) + long(P.a) * P.plane;
+#pragma unroll
+  for (int m = 0; m < R; ++m) {
+    re[m] *= e[m].x;
+    im[m] *= e[m].y;
+    qsum += double(re[m]) + double(im[m]);
   }
-  if ((!P.mid || P.second) && active) {
+  auto store = [&](T* p) {
 #pragma unroll
     for (int m = 0; m < R; ++m) {
-      const long i2 = (long(j + TL * m) * P.nx + x0) >> 1;
       T2<T> o;
       o.x = re[m];
       o.y = im[m];
-      tmp2[i2] = o;
+      st(p, o0 + m * step, o);
     }
+  };
+  if (active) store(qo);
+  if (P.second) {
+    const T* E1 = c == 0 ? P.E[0][1] : P.E[1][1];
+    if (E1 != E0) {
+#pragma unroll
+      for (int m = 0; m < R; ++m) e[m] = ld<T2<T>>(E1, o0 + m * step);
+    }
+#pragma unroll
+    for (int m = 0; m < R; ++m) {
+      re[m] *= e[m].x;
+      im[m] *= e[m].y;
+    }
+    conv();
+    if (active) store(tmp);
   }
   if (P.last) {
-    double v[1] = {qsum};
+    double v[1] = {active ? qsum : 0.0};
     block_partial<1>(v, red, P.partials + c * gridDim.x, tile);
   }
 }
