@@ -14,11 +14,11 @@
 // scratch out; the y pass: scratch in and out).
 //
 // What bounds it: HBM at large sizes (launch latency below about 64^3, where a
-// pass is 6-7 us).  As one three-dimensional complex transform pair per step, a
+// pass is 4-5 us).  As one three-dimensional complex transform pair per step, a
 // chain at a time, a step moved 22 planes per chain in 5 launches.  Measured at
 // 256^3 FP32, N = 32: 320 launches of 120 us, 39.4 ms per evaluation, before;
-// 65 launches of 106 us (403 MB each, 3.8 TB/s; a copy reaches 5.05), 7.9 ms,
-// now.  128^3: 4.99 -> 1.12 ms (FP32), 9.32 -> 1.77 ms (FP64).
+// 65 launches of 83 us (403 MB each, 4.8 TB/s; a copy reaches 5.05), 6.45 ms,
+// now.  128^3: 4.99 -> 1.07 ms (FP32), 9.32 -> 1.74 ms (FP64).
 //
 // The sums (gauge, Q_P, Q_S) are FP64 block partials in fixed slots, added in
 // slot order.
@@ -34,10 +34,12 @@ constexpr int kMaxLen = 512;
 
 // One pass of the propagators: lines of length L along one axis.
 template <typename T> struct PassArgs {
-  const T* wA;
+  const T* wA;          // first pass (and grids of one site)
   const T* wB;
-  T* EA;                // exp(-(w_A - c_A)/2), written by the first pass
+  T* EA;                // first pass: exp(-(w_A - c_A)/2), written for the later ones
   T* EB;
+  T* EJ;                // the same of the junction segment (A fraction fracJ); nullptr: none
+  const T* E[2][2];     // factor plane of chain c at step a (+0/+1): EA, EB or EJ
   const double* sums;   // field sums: [0] w_A, [1] w_B
   double inv_n;
   T* q[2];              // mid: the plane q_{a+1} of each chain
@@ -48,23 +50,25 @@ template <typename T> struct PassArgs {
   long units;           // pairs of lines
   long rows;            // contiguous lines: their number (the last pair may be half empty)
   long inner, gs, st;   // strided lines: pair u starts at (u / inner) gs + 2 (u % inner), element stride st
-  int first;            // input is E(step 0) (q_0 = 1) instead of tmp; writes EA and EB
-  int conv;             // convolve (0: the first pass of a grid with one axis, which only forms E)
+  int conv;             // first pass: convolve (0: a grid with one axis, whose first pass only forms E)
   int mid;              // after the convolution: x E(step a), store q_{a+1}
   int second;           // then x E(step a + 1) and convolve again (2: no convolution, one axis)
   int last;             // with mid: partial sums of q_N
-  T frac[2][2];         // A fraction of the segment of chain c at step a (+0/+1)
+  T frac[2];            // first pass: A fraction of chain c's segment at step 0
+  T fracJ;
   double* partials;     // last: per-block sums of q_N of the forward chain
 };
 
-// Transforms per block of a pass over strided lines: 256 or 512 lanes, and
+// Transforms per block of a pass over strided lines.  Wide: 256 or 512 lanes, and
 // neighbouring lanes on neighbouring pairs: 128-byte segments (a whole cache
 // line) for lengths up to 256 in FP32 and 512 in FP64 (64 bytes at 512 in FP32,
-// where 16 pairs would need 1,024 lanes).
-template <typename T, int L, int R> constexpr int strided_nf() {
+// where 16 pairs would need 1,024 lanes).  Narrow: one wave (at least four pairs),
+// for grids whose wide blocks would leave CUs idle.
+template <typename T, int L, int R> constexpr int strided_nf(bool wide) {
   constexpr int tl = L / R;
-  constexpr int wide = sizeof(T) == 4 ? 16 : 8;   // pairs of one 128-byte segment
-  return tl * wide <= 256 ? 256 / tl : (tl * wide <= 512 ? wide : 512 / tl);
+  constexpr int seg = sizeof(T) == 4 ? 16 : 8;   // pairs of one 128-byte segment
+  if (!wide) return tl * 4 <= 64 ? 64 / tl : 4;
+  return tl * seg <= 256 ? 256 / tl : (tl * seg <= 512 ? seg : 512 / tl);
 }
 // Values per lane: whole short lines, else 8.
 template <int L> constexpr int values_per_lane() { return L < 8 ? L : 8; }
@@ -95,9 +99,17 @@ __device__ __forceinline__ void convolve_exact(T* re, T* im, int j, const V& lds
 
 // CONTIG: lines along x, two neighbouring rows per transform, nf = blockDim /
 // (L/R) transforms per block.  Otherwise lines along y or z, columns x, x + 1
-// per transform, NF transforms per block interleaved lane by lane.
-template <typename T, int L, int R, bool CONTIG, int NF>
-__global__ void __launch_bounds__(512) k_p3_pass(PassArgs<T> P) {
+// per transform, NF transforms per block interleaved lane by lane.  The code path
+// is kept straight as in the two-dimensional passes: the first pass is an
+// instantiation of its own, factors come from one plane per step, every load is
+// unconditional (a transform past the end repeats the last one and stores
+// nothing), offsets are 32 bits (a plane is at most 2^27 sites).  With the factor
+// chosen by a branch per value, 64 x 32 x 16 FP64 at N = 16 took 0.237 ms, and
+// 0.196 ms now.  FP32 is held to 128 registers, four waves per SIMD: at 256^3 the
+// 129th cost 8.08 against 6.45 ms.
+template <typename T, int L, int R, bool CONTIG, int NF, bool FIRST>
+__global__ void __launch_bounds__(512, sizeof(T) == 4 ? 4 : 2) k_p3_pass(PassArgs<T> P) {
+  static_assert(CONTIG || !FIRST, "the first pass runs along x");
   constexpr int TL = L / R;
   using V = LdsView<T, L, R, CONTIG, NF>;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -108,63 +120,77 @@ __global__ void __launch_bounds__(512) k_p3_pass(PassArgs<T> P) {
   V lds{reinterpret_cast<T2<T>*>(smem_raw), f};
   const int lt = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
   const int c = lt / gridDim.x, tile = lt % gridDim.x;
-  const long u = long(tile) * nf + f;
-  const bool active = u < P.units;
-  // the two real lines: element e at i0 + e st and i1 + e st
-  long i0 = 0, i1 = 0;
+  const unsigned want = unsigned(tile) * nf + f, u = min(want, unsigned(P.units) - 1u);
+  const bool active = want == u;
+  // element m of this lane: byte offset o0 + m step, and o1 + m step in the
+  // second line (strided lines: the pair is one aligned access at o0)
+  unsigned o0, o1 = 0, step;
   bool two = active;
-  if (active) {
-    if constexpr (CONTIG) {
-      i0 = 2 * u * L;
-      i1 = i0 + L;
-      two = 2 * u + 1 < P.rows;
-    } else {
-      i0 = (u / P.inner) * P.gs + 2 * (u % P.inner);
-    }
+  if constexpr (CONTIG) {
+    o0 = (2u * u * L + j) * unsigned(sizeof(T));
+    const bool has = 2u * u + 1u < unsigned(P.rows);
+    o1 = has ? o0 + L * unsigned(sizeof(T)) : o0;
+    two = active && has;
+    step = TL * sizeof(T);
+  } else {
+    const unsigned in = unsigned(P.inner), g = u / in;
+    o0 = (g * unsigned(P.gs) + 2u * (u - g * in) + unsigned(j) * unsigned(P.st)) * unsigned(sizeof(T));
+    step = unsigned(TL) * unsigned(P.st) * unsigned(sizeof(T));
   }
-  const long st = CONTIG ? 1 : P.st;
-  const T ca = T(P.sums[0] * P.inv_n), cb = T(P.sums[1] * P.inv_n);
-  const T fr0 = c == 0 ? P.frac[0][0] : P.frac[1][0], fr1 = c == 0 ? P.frac[0][1] : P.frac[1][1];
-  // both lines' values at element e; the strided pair is one aligned load
-  auto load2 = [&](const T* p, int e, T& a, T& b) {
+  auto load2 = [&](const T* p, int m, T& a, T& b) {
     if constexpr (CONTIG) {
-      a = active ? p[i0 + e] : T(0);
-      b = two ? p[i1 + e] : T(0);
+      a = ld<T>(p, o0 + m * step);
+      b = ld<T>(p, o1 + m * step);
     } else {
-      T2<T> v;
-      v.x = v.y = T(0);
-      if (active) v = *reinterpret_cast<const T2<T>*>(p + i0 + e * st);
+      const T2<T> v = ld<T2<T>>(p, o0 + m * step);
       a = v.x;
       b = v.y;
     }
   };
-  auto store2 = [&](T* p, int e, T a, T b) {
+  auto store2 = [&](T* p, int m, T a, T b) {
     if constexpr (CONTIG) {
-      if (active) p[i0 + e] = a;
-      if (two) p[i1 + e] = b;
+      if (active) st(p, o0 + m * step, a);
+      if (two) st(p, o1 + m * step, b);
     } else if (active) {
       T2<T> v;
       v.x = a;
       v.y = b;
-      *reinterpret_cast<T2<T>*>(p + i0 + e * st) = v;
+      st(p, o0 + m * step, v);
     }
   };
-  auto factor2 = [&](T fr, int e, T& a, T& b) {
-    if (fr == T(1)) {
-      load2(P.EA, e, a, b);
-    } else if (fr == T(0)) {
-      load2(P.EB, e, a, b);
-    } else {
+  T* tmp = P.tmp + c * P.n;
+  T re[R], im[R], ea[R], eb[R];
+  if constexpr (FIRST) {
+    // the factor planes of the later passes: A's from the forward chain's
+    // blocks, B's from the backward chain's
+    const T ca = T(P.sums[0] * P.inv_n), cb = T(P.sums[1] * P.inv_n);
+    const T fr0 = c == 0 ? P.frac[0] : P.frac[1];
+    const T pure = c == 0 ? T(1) : T(0);
+    T* Ep = c == 0 ? P.EA : P.EB;
+#pragma unroll
+    for (int m = 0; m < R; ++m) {
       T ua, ub, va, vb;
-      load2(P.wA, e, ua, ub);
-      load2(P.wB, e, va, vb);
-      a = boltz(ua, va, fr, ca, cb);
-      b = boltz(ub, vb, fr, ca, cb);
+      load2(P.wA, m, ua, ub);
+      load2(P.wB, m, va, vb);
+      const T p0 = boltz(ua, va, pure, ca, cb), p1 = boltz(ub, vb, pure, ca, cb);
+      store2(Ep, m, p0, p1);
+      if (c == 0 && P.EJ) store2(P.EJ, m, boltz(ua, va, P.fracJ, ca, cb), boltz(ub, vb, P.fracJ, ca, cb));
+      re[m] = fr0 == pure ? p0 : boltz(ua, va, fr0, ca, cb);
+      im[m] = fr0 == pure ? p1 : boltz(ub, vb, fr0, ca, cb);
     }
-  };
+  } else {
+    const T* E0 = c == 0 ? P.E[0][0] : P.E[1][0];
+#pragma unroll
+    for (int m = 0; m < R; ++m) load2(tmp, m, re[m], im[m]);
+    if (P.mid) {  // loaded before the transform, so that the latency overlaps it
+#pragma unroll
+      for (int m = 0; m < R; ++m) load2(E0, m, ea[m], eb[m]);
+    }
+  }
   // twiddles into LDS, behind the transforms' buffer
   T2<T>* twl = reinterpret_cast<T2<T>*>(smem_raw) + (L > R ? V::size_elems(nf) : 0);
   for (int i = threadIdx.x; i < TwTables<T, L, R>::kElems; i += blockDim.x) twl[i] = P.tw[i];
+  if constexpr (V::kSync != kSyncBlock && L > R) __syncthreads();  // the exchanges have no barrier of the block
   const TwTables<T, L, R> tw{twl};
   T g[R], gl[R];
 #pragma unroll
@@ -172,49 +198,23 @@ __global__ void __launch_bounds__(512) k_p3_pass(PassArgs<T> P) {
     g[m] = P.mult[j + TL * m];
     gl[m] = sizeof(T) == 4 ? P.mult[L + j + TL * m] : T(0);
   }
-  T* tmp = P.tmp + c * P.n;
-  T re[R], im[R], ea[R], eb[R];
-  if (P.first) {
-    // the factor planes of the later passes: A's from the forward chain's
-    // blocks, B's from the backward chain's
-    const T pure = c == 0 ? T(1) : T(0);
-    T* Ep = c == 0 ? P.EA : P.EB;
-#pragma unroll
-    for (int m = 0; m < R; ++m) {
-      const int e = j + TL * m;
-      T ua, ub, va, vb;
-      load2(P.wA, e, ua, ub);
-      load2(P.wB, e, va, vb);
-      const T p0 = boltz(ua, va, pure, ca, cb), p1 = boltz(ub, vb, pure, ca, cb);
-      store2(Ep, e, p0, p1);
-      re[m] = fr0 == pure ? p0 : boltz(ua, va, fr0, ca, cb);
-      im[m] = fr0 == pure ? p1 : boltz(ub, vb, fr0, ca, cb);
-      if (!active) re[m] = T(0);
-      if (!two) im[m] = T(0);
-    }
-  } else {
-#pragma unroll
-    for (int m = 0; m < R; ++m) load2(tmp, j + TL * m, re[m], im[m]);
-  }
-  if (P.mid) {  // loaded before the transform, so that the latency overlaps it
-#pragma unroll
-    for (int m = 0; m < R; ++m) factor2(fr0, j + TL * m, ea[m], eb[m]);
-  }
-  if (P.conv) convolve_exact<T, L, R>(re, im, j, lds, tw, g, gl);
+  if (!FIRST || P.conv) convolve_exact<T, L, R>(re, im, j, lds, tw, g, gl);
   double qsum = 0.0;
-  if (P.mid) {
+  if (!FIRST && P.mid) {
     T* qo = c == 0 ? P.q[0] : P.q[1];
 #pragma unroll
     for (int m = 0; m < R; ++m) {
       re[m] *= ea[m];
       im[m] *= eb[m];
-      store2(qo, j + TL * m, re[m], im[m]);
-      qsum += double(re[m]) + double(im[m]);
+      store2(qo, m, re[m], im[m]);
+      qsum += (active ? double(re[m]) : 0.0) + (two ? double(im[m]) : 0.0);
     }
     if (P.second) {
-      if (fr1 != fr0) {
+      const T* E0 = c == 0 ? P.E[0][0] : P.E[1][0];
+      const T* E1 = c == 0 ? P.E[0][1] : P.E[1][1];
+      if (E1 != E0) {
 #pragma unroll
-        for (int m = 0; m < R; ++m) factor2(fr1, j + TL * m, ea[m], eb[m]);
+        for (int m = 0; m < R; ++m) load2(E1, m, ea[m], eb[m]);
       }
 #pragma unroll
       for (int m = 0; m < R; ++m) {
@@ -224,11 +224,11 @@ __global__ void __launch_bounds__(512) k_p3_pass(PassArgs<T> P) {
       if (P.second == 1) convolve_exact<T, L, R>(re, im, j, lds, tw, g, gl);
     }
   }
-  if (!P.mid || P.second) {
+  if (FIRST || !P.mid || P.second) {
 #pragma unroll
-    for (int m = 0; m < R; ++m) store2(tmp, j + TL * m, re[m], im[m]);
+    for (int m = 0; m < R; ++m) store2(tmp, m, re[m], im[m]);
   }
-  if (P.last && c == 0) {
+  if (!FIRST && P.last && c == 0) {
     double v[1] = {qsum};
     block_partial<1>(v, red, P.partials, tile);
   }
@@ -236,11 +236,11 @@ __global__ void __launch_bounds__(512) k_p3_pass(PassArgs<T> P) {
 
 // A grid of one site: K is the identity, q_{j+1} = E_j^2 q_j.
 template <typename T>
-__global__ void k_p3_one(PassArgs<T> P, T* q, int chain) {
+__global__ void k_p3_one(PassArgs<T> P, T* q, int chain, int first) {
   if (threadIdx.x || blockIdx.x) return;
   const T ca = T(P.sums[0] * P.inv_n), cb = T(P.sums[1] * P.inv_n);
-  const T e = boltz(P.wA[0], P.wB[0], P.frac[chain][0], ca, cb);
-  q[0] = e * (e * (P.first ? T(1) : P.tmp[chain]));
+  const T e = boltz(P.wA[0], P.wB[0], P.frac[chain], ca, cb);
+  q[0] = e * (e * (first ? T(1) : P.tmp[chain]));
   P.tmp[chain] = q[0];
   if (P.last && chain == 0) P.partials[0] = double(q[0]);
 }

@@ -3558,31 +3558,43 @@ namespace {
 
 bool pow2_upto(int v, int m) { return v >= 1 && v <= m && (v & (v - 1)) == 0; }
 
-// Blocks per chain of a pass along `axis` over lines of length L.
-template <typename T, int L, bool CONTIG> struct P3Shape {
-  static constexpr int R = epd3::values_per_lane<L>();
-  static constexpr int nf = CONTIG ? 256 / (L / R) : epd3::strided_nf<T, L, R>();
-  static constexpr int threads = nf * (L / R);
+template <typename T, int L, bool CONTIG, int NF, bool FIRST>
+int p3_launch(const epd3::PassArgs<T>& a, hipStream_t s, int nf, long blocks) {
+  constexpr int R = epd3::values_per_lane<L>();
   // the transforms' exchange buffer, then the twiddles; none for one-pass transforms
-  static constexpr size_t lds =
-      L > R ? (LdsView<T, L, R, CONTIG, CONTIG ? 1 : nf>::size_elems(nf) + TwTables<T, L, R>::kElems) * sizeof(T2<T>)
-            : 0;
-};
-
-template <typename T, int L, bool CONTIG>
-int p3_pass_shape(const epd3::PassArgs<T>* a, hipStream_t s, long units, long* blocks) {
-  using S = P3Shape<T, L, CONTIG>;
-  *blocks = (units + S::nf - 1) / S::nf;
-  if (!a) return EPDLB_OK;
-  auto k = epd3::k_p3_pass<T, L, S::R, CONTIG, CONTIG ? 1 : S::nf>;
-  HIPCHK(prep_lds(k, S::lds));
-  launch_k(k, dim3(unsigned(*blocks), 2), dim3(S::threads), S::lds, s, *a);
+  const size_t lds =
+      L > R ? (LdsView<T, L, R, CONTIG, NF>::size_elems(nf) + TwTables<T, L, R>::kElems) * sizeof(T2<T>) : 0;
+  auto k = epd3::k_p3_pass<T, L, R, CONTIG, NF, FIRST>;
+  HIPCHK(prep_lds(k, lds));
+  launch_k(k, dim3(unsigned(blocks), 2), dim3(unsigned(nf * (L / R))), lds, s, a);
   HIPCHK(hipGetLastError());
   return EPDLB_OK;
 }
+// Launches a pass over `units` pairs of lines of length L (a = nullptr: only its
+// blocks per chain).  Blocks are wide where both chains together still give two per
+// CU, else one wave, so that a small grid reaches more CUs.  An evaluation with
+// wide / narrow blocks: 64 x 32 x 16 FP64, N = 16: 0.196 / 0.155 ms; 64^3 FP32,
+// N = 32: 0.368 / 0.338; 128^3: 1.07 / 1.23 (FP64 1.74 / 1.86); 256^3: 6.45 / 8.02
+// (wide blocks read whole cache lines along y and z).
+template <typename T, int L, bool CONTIG>
+int p3_pass_shape(const epd3::PassArgs<T>* a, bool first, hipStream_t s, long units, long* blocks) {
+  constexpr int R = epd3::values_per_lane<L>(), tl = L / R;
+  constexpr int wide = CONTIG ? 256 / tl : epd3::strided_nf<T, L, R>(true);
+  constexpr int narrow = CONTIG ? (tl <= 64 ? 64 / tl : 1) : epd3::strided_nf<T, L, R>(false);
+  const bool w = (units + wide - 1) / wide >= 256;
+  const int nf = w ? wide : narrow;
+  *blocks = (units + nf - 1) / nf;
+  if (!a) return EPDLB_OK;
+  if constexpr (CONTIG) {
+    return first ? p3_launch<T, L, true, 1, true>(*a, s, nf, *blocks) : p3_launch<T, L, true, 1, false>(*a, s, nf, *blocks);
+  } else {
+    return w ? p3_launch<T, L, false, wide, false>(*a, s, nf, *blocks)
+             : p3_launch<T, L, false, narrow, false>(*a, s, nf, *blocks);
+  }
+}
 
 // One pass along axis `ax` of the grid (a = nullptr: only its blocks per chain).
-template <typename T> int p3_pass(epdlb_epd3* c, int ax, epd3::PassArgs<T>* a, long* blocks) {
+template <typename T> int p3_pass(epdlb_epd3* c, int ax, epd3::PassArgs<T>* a, long* blocks, bool first = false) {
   const int L = c->len[ax];
   const long lines = c->n / L;
   const long units = (lines + 1) / 2;
@@ -3604,8 +3616,8 @@ template <typename T> int p3_pass(epdlb_epd3* c, int ax, epd3::PassArgs<T>* a, l
   }
 #define EPDLB_P3_L(len)                                                                     \
   case len:                                                                                 \
-    return ax == 0 ? p3_pass_shape<T, len, true>(a, c->stream, units, blocks)               \
-                   : p3_pass_shape<T, len, false>(a, c->stream, units, blocks);
+    return ax == 0 ? p3_pass_shape<T, len, true>(a, first, c->stream, units, blocks)        \
+                   : p3_pass_shape<T, len, false>(a, first, c->stream, units, blocks);
   switch (L) {
     EPDLB_P3_L(2)
     EPDLB_P3_L(4)
@@ -3654,24 +3666,28 @@ template <typename T> int p3_densities(epdlb_epd3* c) {
   A.n = n;
   A.partials = c->part;
   auto seg = [&](int chain, int step) { return T(c->seg[chain ? N - 1 - step : step]); };
+  // the junction segment's factors lie in the densities' first plane until those are formed
+  T* junction = static_cast<T*>(c->phi);
+  for (int j = 0; j < N; ++j)
+    if (T(c->seg[j]) != T(0) && T(c->seg[j]) != T(1)) {
+      A.EJ = junction;
+      A.fracJ = T(c->seg[j]);
+    }
+  auto plane_of = [&](T fr) { return (const T*)(fr == T(1) ? A.EA : fr == T(0) ? A.EB : junction); };
   long blocks = 1;
   if (c->ndim == 0) {
     for (int s = 0; s < N; ++s)
       for (int ch = 0; ch < 2; ++ch) {
-        A.first = s == 0;
         A.last = s + 1 == N;
-        A.frac[ch][0] = seg(ch, s);
-        launch_k((epd3::k_p3_one<T>), dim3(1), dim3(64), 0, c->stream, A, q[ch] + s, ch);
+        A.frac[ch] = seg(ch, s);
+        launch_k((epd3::k_p3_one<T>), dim3(1), dim3(64), 0, c->stream, A, q[ch] + s, ch, int(s == 0));
         HIPCHK(hipGetLastError());
       }
   } else {
     // step 0: its first convolution, of E(step 0); with one axis only E itself
-    A.first = 1;
     A.conv = c->ndim > 1;
-    for (int ch = 0; ch < 2; ++ch) A.frac[ch][0] = A.frac[ch][1] = seg(ch, 0);
-    CHK(p3_pass<T>(c, 0, &A, &blocks));
-    A.first = 0;
-    A.conv = 1;
+    for (int ch = 0; ch < 2; ++ch) A.frac[ch] = seg(ch, 0);
+    CHK(p3_pass<T>(c, 0, &A, &blocks, true));
     for (int s = 0; s < N; ++s) {
       // the convolutions of step s between its first and its last
       A.mid = A.second = A.last = 0;
@@ -3682,8 +3698,8 @@ template <typename T> int p3_densities(epdlb_epd3* c) {
       A.last = s + 1 == N;
       for (int ch = 0; ch < 2; ++ch) {
         A.q[ch] = q[ch] + long(s) * n;
-        A.frac[ch][0] = seg(ch, s);
-        A.frac[ch][1] = s + 1 < N ? seg(ch, s + 1) : seg(ch, s);
+        A.E[ch][0] = plane_of(seg(ch, s));
+        A.E[ch][1] = s + 1 < N ? plane_of(seg(ch, s + 1)) : A.E[ch][0];
       }
       CHK(p3_pass<T>(c, p3_axis(c, s, c->ndim - 1), &A, &blocks));
     }

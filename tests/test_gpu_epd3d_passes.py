@@ -39,3 +39,11 @@ def test_passes_vs_oracle(shape, N, fA, prec):
         assert err < tol, (err, tol)
         assert abs(QP / ref["Q_P"] - 1) < tol and abs(QS / ref["Q_S"] - 1) < tol
     d.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("shape,N,fA", [((64, 128, 128), 3, 0.5), ((4, 512, 512), 2, 0.3), ((512, 512, 2), 2, 0.5),
+                                        ((32, 128, 128), 2, 0.3)])
+def test_wide_and_narrow_blocks_vs_oracle(shape, N, fA, prec):
+    """Grids on both sides of the block rule (two wide blocks per CU), each axis on its own side."""
+    test_passes_vs_oracle(shape, N, fA, prec)
