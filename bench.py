@@ -67,11 +67,7 @@ NN_FLOPS_PER_SITE = {"nn_conv0": 9 * 5 * 64 * 2, "nn_conv": 9 * 64 * 64 * 2}
 # WRITE x1.0); the summaries with their commands are under profiles/.  An
 # entry holds only while the sources its kernels are built from hash to
 # `source_sha256`; otherwise the bench reports null.
-MEASURED_TRAFFIC = {
-    # profiles/lb3_fluid3d_256_traffic.md: the step kernel without moment stores
-    ("fluid3d_256", "lb3"): dict(bytes_per_launch=2873793431, files=("lb3.hpp",),
-                                 source_sha256="e7e59f031e128b313dda272b0a26b0ab5c5fe413ad9252a506d9b009c091450e"),
-}
+MEASURED_TRAFFIC = {}
 
 
 def kernel_source_sha256(files):

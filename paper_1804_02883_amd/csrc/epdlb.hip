@@ -3260,35 +3260,48 @@ template <typename T> lb3::Lb3Args<T> lb3_args(epdlb_lb3* c, int from) {
   a.n = c->n;
   a.omega = T(1.0 / c->tau);
   a.fpre = T(1.0 - 0.5 / c->tau);
+  a.by_nx = lb3::DivBy(c->nx);
+  a.by_ny = lb3::DivBy(c->ny);
   return a;
 }
 
-dim3 lb3_grid(const epdlb_lb3* c) { return dim3((c->ny + lb3::kRows - 1) / lb3::kRows, c->nz); }
+template <typename T, typename Off, int BLOCK, typename Args>
+void lb3_run(epdlb_lb3* c, const Args& a, bool mom) {
+  const long blocks = (c->n + BLOCK - 1) / BLOCK;
+  const dim3 grid(unsigned((blocks + kNumXcd - 1) / kNumXcd * kNumXcd));
+  if (mom)
+    launch_k((lb3::k_lb3<T, Args, Off, true, BLOCK>), grid, dim3(BLOCK), 0, c->stream, a);
+  else
+    launch_k((lb3::k_lb3<T, Args, Off, false, BLOCK>), grid, dim3(BLOCK), 0, c->stream, a);
+}
+
+template <typename T, typename Args> int lb3_form(epdlb_lb3* c, const Args& a, bool mom) {
+  if (size_t(c->n) * sizeof(T) > size_t(UINT32_MAX))
+    lb3_run<T, size_t, lb3::kThreads>(c, a, mom);
+  else if (c->n > lb3::kSmall)
+    lb3_run<T, unsigned, lb3::kThreads>(c, a, mom);
+  else
+    lb3_run<T, unsigned, lb3::kThreadsSmall>(c, a, mom);
+  HIPCHK(hipGetLastError());
+  c->cur ^= 1;
+  return EPDLB_OK;
+}
 
 // One step from f[cur] into f[cur ^ 1]; the moments are stored when mom.
 template <typename T> int lb3_launch(epdlb_lb3* c, bool mom) {
   const auto a = lb3_args<T>(c, c->cur);
-  if (c->mrt) {
-    lb3::Lb3MrtArgs<T> m;
-    m.b = a;
-    m.gs = T(c->gs);
-    m.gb = T(c->gb);
-    m.gg = T(c->gg);
-    if (mom)
-      launch_k((lb3::k_lb3_mrt<T, true>), lb3_grid(c), dim3(lb3::kThreads), 0, c->stream, m);
-    else
-      launch_k((lb3::k_lb3_mrt<T, false>), lb3_grid(c), dim3(lb3::kThreads), 0, c->stream, m);
-    HIPCHK(hipGetLastError());
-    c->cur ^= 1;
-    return EPDLB_OK;
-  }
-  if (mom)
-    launch_k((lb3::k_lb3<T, true>), lb3_grid(c), dim3(lb3::kThreads), 0, c->stream, a);
-  else
-    launch_k((lb3::k_lb3<T, false>), lb3_grid(c), dim3(lb3::kThreads), 0, c->stream, a);
-  HIPCHK(hipGetLastError());
-  c->cur ^= 1;
-  return EPDLB_OK;
+  if (!c->mrt) return lb3_form<T>(c, a, mom);
+  lb3::Lb3MrtArgs<T> m;
+  m.b = a;
+  m.gs = T(c->gs);
+  m.gb = T(c->gb);
+  m.gg = T(c->gg);
+  return lb3_form<T>(c, m, mom);
+}
+
+template <typename T> void lb3_equilibrium(epdlb_lb3* c) {
+  launch_k((lb3::k_lb3_equilibrium<T>), dim3(unsigned((c->n + lb3::kThreads - 1) / lb3::kThreads)),
+           dim3(lb3::kThreads), 0, c->stream, lb3_args<T>(c, c->cur ^ 1));
 }
 
 int lb3_steps(epdlb_lb3* c, int64_t n, hipEvent_t* ev) {
@@ -3423,9 +3436,9 @@ int epdlb_lb3_set_equilibrium(epdlb_lb3* c, const double* rho, const double* u) 
   }
   // the arguments of a step from f[cur ^ 1] write f[cur], the state
   if (c->precision)
-    launch_k((lb3::k_lb3_equilibrium<float>), lb3_grid(c), dim3(lb3::kThreads), 0, c->stream, lb3_args<float>(c, c->cur ^ 1));
+    lb3_equilibrium<float>(c);
   else
-    launch_k((lb3::k_lb3_equilibrium<double>), lb3_grid(c), dim3(lb3::kThreads), 0, c->stream, lb3_args<double>(c, c->cur ^ 1));
+    lb3_equilibrium<double>(c);
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(c->stream));
   c->have_moments = false;
