@@ -67,7 +67,11 @@ NN_FLOPS_PER_SITE = {"nn_conv0": 9 * 5 * 64 * 2, "nn_conv": 9 * 64 * 64 * 2}
 # WRITE x1.0); the summaries with their commands are under profiles/.  An
 # entry holds only while the sources its kernels are built from hash to
 # `source_sha256`; otherwise the bench reports null.
-MEASURED_TRAFFIC = {}
+MEASURED_TRAFFIC = {
+    # profiles/lb3_fluid3d_256_traffic.md: the step kernel without moment stores
+    ("fluid3d_256", "lb3"): dict(bytes_per_launch=2751540306, files=("lb3.hpp",),
+                                 source_sha256="00612d3692132a490494ae8af15af4cd91f576f0cf2aeadfdd24c455de263e97"),
+}
 
 
 def kernel_source_sha256(files):

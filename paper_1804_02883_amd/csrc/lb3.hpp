@@ -13,12 +13,14 @@
 // The step moves 19 values in and 19 out per site plus the force: it is a
 // streaming kernel bound by HBM.  Each value is read by exactly one site (the
 // one its velocity points to), so the only reuse is the cache line that two
-// neighbouring chunks share when a population moves along x; consecutive blocks
-// run on one XCD, whose L2 then holds that line.  A lane takes one site, in the
-// order of memory: every wave but the last is full whatever the row length, and
-// all sites are in flight at once.  With a wave per row, in chunks of 64 sites,
-// a row of 70 left 45 % of the lanes idle.  Per step, before -> now: 192^3 FP32
-// 229.8 -> 224.4 us (5.2 TB/s); 190^3 FP32 331 -> 227; 100^3 FP64 70.0 -> 59.9;
+// neighbouring chunks share when a population moves along x; runs of 4,096 sites
+// stay on one XCD, whose L2 then holds that line (192^3 / 256^3 FP32: 214.9 /
+// 520 us a step; one run per XCD through the whole box 225.3 / 525, single
+// blocks 218.1 / 505 but 128^3 FP64 138.8 against 133.9).  A lane takes one site,
+// in the order of memory: every wave but the last is full whatever the row length,
+// and all sites are in flight at once.  With a wave per row, in chunks of 64
+// sites, a row of 70 left 45 % of the lanes idle.  Per step, before -> now: 192^3
+// FP32 229.8 -> 214.9 us (5.4 TB/s); 190^3 FP32 331 -> 213; 100^3 FP64 70.0 -> 56.2;
 // 70 x 45 x 33 FP64 11.9 -> 6.3; 32^3 FP32 3.6 -> 3.2.
 #pragma once
 #include "kernels.hpp"
@@ -132,12 +134,24 @@ __device__ __forceinline__ void collide(const Lb3Args<T>& P, const T (&g)[kQ], O
   }
 }
 
-// One step at every site.  Grid: n / BLOCK blocks, rounded up to all XCDs.
+// The block of sites a block takes.  Large boxes: runs of 4,096 sites on one XCD
+// (block b starts on XCD b mod 8), the XCDs side by side through memory.  Small
+// ones: one run per XCD, whose L2 then still holds most of what the last step
+// wrote (70 x 45 x 33 FP64: 6.4 us, 8.2 in runs of 4,096).
+template <int BLOCK> __device__ __forceinline__ unsigned site_block(unsigned b, unsigned blocks) {
+  if constexpr (BLOCK == kThreadsSmall) return xcd_tile(b, blocks);
+  constexpr unsigned run = 4096 / BLOCK, group = kNumXcd * run;
+  if (b >= blocks / group * group) return b;
+  const unsigned r = b % group;
+  return b - r + (r % kNumXcd) * run + r / kNumXcd;
+}
+
+// One step at every site: ceil(n / BLOCK) blocks, rounded up to all XCDs.
 template <typename T, typename Args, typename Off, bool MOM, int BLOCK>
 __global__ void __launch_bounds__(BLOCK) k_lb3(Args A) {
   const Lb3Args<T>& P = A.base();
   const unsigned nx = P.nx, ny = P.ny, nz = P.nz;
-  const unsigned i = unsigned(xcd_tile(blockIdx.x, gridDim.x)) * BLOCK + threadIdx.x;
+  const unsigned i = site_block<BLOCK>(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
   if (i >= unsigned(P.n)) return;
   const unsigned r = P.by_nx(i), x = i - r * nx, z = P.by_ny(r), y = r - z * ny;
   // byte distance to the sites that populations with components +1, 0, -1 come
