@@ -1589,22 +1589,23 @@ int check_finite(epdlb_ctx* c) {
 
 // ---------------------------------------------------------------------------
 // Batched replicas: replicas of one grid shape form a group that shares every
-// launch (blockIdx.z = replica); groups are independent branches of one
-// captured graph per step pair, forked from and joined to the batch stream.
+// launch (blockIdx.z = replica).  A step is a chain of some N + 7 short launches
+// that each leave most of the chip idle, so groups run side by side, on streams that
+// each take the captured graphs of their groups one after another, forked from and
+// joined to the batch stream once per call.  16 replicas in 8 groups of 4 grids (64^2
+// to 512 x 256, FP32, N = 32), per step: 1,105 us as parallel branches of one graph
+// per step pair (711 us with the shorter passes, 590 of them the host's submission),
+// 590 us now.  What is left over the longest stream's 380 us is the groups' rivalry
+// for CUs.
 // ---------------------------------------------------------------------------
 struct epdlb_batch {
   int device = 0;
   hipStream_t stream = nullptr;
   bool own_stream = false;
+  static constexpr size_t kLanes = 4;  // hardware queues of a process
+  std::vector<hipStream_t> lanes;      // the groups' streams; the batch stream for a single group
   std::vector<epdlb_ctx*> groups;
   std::vector<std::pair<int, int>> where;  // replica -> (group, index in group)
-  struct G {
-    int steps;
-    hipGraphExec_t exec;
-  };
-  std::vector<G> graphs;
-  hipStream_t cap = nullptr;
-  std::vector<hipStream_t> fork;
   hipEvent_t ev_fork = nullptr;
   std::vector<hipEvent_t> ev_join;
   int64_t nstep = 0;
@@ -1624,8 +1625,8 @@ bool same_model(const epdlb_params& a, const epdlb_params& b) {
          a.mach_max == b.mach_max;
 }
 
-// A group context over `rp` (same grid shape), arena allocated here.
-int make_group(const std::vector<epdlb_params>& rp, int device, epdlb_ctx** out) {
+// A group context over `rp` (same grid shape) on `stream`, arena allocated here.
+int make_group(const std::vector<epdlb_params>& rp, int device, hipStream_t stream, epdlb_ctx** out) {
   epdlb_ctx* c = new (std::nothrow) epdlb_ctx();
   if (!c) return fail(EPDLB_ENOMEM, "host allocation failed");
   c->p = rp[0];
@@ -1636,11 +1637,7 @@ int make_group(const std::vector<epdlb_params>& rp, int device, epdlb_ctx** out)
   if (const char* env = std::getenv("EPDLB_SUR_GRAPH")) c->sur_graph = std::atoi(env) != 0;
   c->L = make_layout(c->p);
   c->rstride = c->L.total;
-  if (hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking) != hipSuccess) {
-    delete c;
-    return fail(EPDLB_EHIP, "hipStreamCreate failed");
-  }
-  c->own_stream = true;
+  c->stream = stream;
   void* m = nullptr;
   if (hipMalloc(&m, c->rstride * c->nrep) != hipSuccess) {
     epdlb_destroy(c);
@@ -1658,71 +1655,92 @@ int make_group(const std::vector<epdlb_params>& rp, int device, epdlb_ctx** out)
   return EPDLB_OK;
 }
 
-void drop_batch_graphs(epdlb_batch* b) {
-  for (auto& g : b->graphs) (void)hipGraphExecDestroy(g.exec);
-  b->graphs.clear();
+// A group's step in us, as measured for single groups: a resident chain takes
+// about 2.8 per contour step, a pass 4.2 and another one per 125,000 FP32 sites.
+double group_cost(const epdlb_ctx* c) {
+  const int N = c->p.n_contour;
+  if (resident(c->p)) return 30.0 + 2.8 * N;
+  return (N + 7) * (4.2 + 2e-6 * elem(c) * double(c->nrep) * c->p.nx * c->p.ny);
 }
 
-// One graph of `steps` steps of every group, groups as parallel branches.
-int batch_graph(epdlb_batch* b, int steps, hipGraphExec_t* out) {
-  for (auto& g : b->graphs)
-    if (g.steps == steps) {
-      *out = g.exec;
-      return EPDLB_OK;
-    }
-  const size_t G = b->groups.size();
-  if (!b->cap) {
-    HIPCHK(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking));
-    HIPCHK(hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming));
-    b->fork.resize(G);
-    b->ev_join.resize(G);
-    for (size_t i = 0; i < G; ++i) {
-      HIPCHK(hipStreamCreateWithFlags(&b->fork[i], hipStreamNonBlocking));
-      HIPCHK(hipEventCreateWithFlags(&b->ev_join[i], hipEventDisableTiming));
-    }
+// Streams for up to kLanes groups at a time.  The runtime gives a new stream the
+// hardware queue with the fewest streams, so four streams made in a row lie on four
+// queues once the queues are level; before, two may meet (the first batch of a
+// process then ran 1,000 us a step instead of 590).  Streams that live only while
+// the lanes are made level them.
+int make_lanes(epdlb_batch* b, size_t groups) {
+  if (groups == 1) {  // nothing to overlap: no fork and join
+    b->lanes.push_back(b->stream);
+    return EPDLB_OK;
   }
-  std::vector<int> cur0(G), fcur0(G);
-  std::vector<hipStream_t> own(G);
-  for (size_t i = 0; i < G; ++i) {
-    cur0[i] = b->groups[i]->cur;
-    fcur0[i] = b->groups[i]->fcur;
-    own[i] = b->groups[i]->stream;
-    b->groups[i]->stream = b->fork[i];
-    b->groups[i]->prof_on = false;
+  std::vector<hipStream_t> level;
+  hipError_t e = hipSuccess;
+  for (size_t i = 0; i < 2 * epdlb_batch::kLanes && e == hipSuccess; ++i) {
+    hipStream_t s;
+    e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    if (e == hipSuccess) level.push_back(s);
   }
-  HIPCHK(hipStreamBeginCapture(b->cap, hipStreamCaptureModeRelaxed));
+  while (e == hipSuccess && b->lanes.size() < std::min(groups, epdlb_batch::kLanes)) {
+    hipStream_t s;
+    e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    if (e == hipSuccess) b->lanes.push_back(s);
+  }
+  for (auto s : level) (void)hipStreamDestroy(s);
+  return e == hipSuccess ? EPDLB_OK : fail(EPDLB_EHIP, "hipStreamCreate failed");
+}
+
+// Groups to lanes, the longest first to the lane with the least to do.
+void spread_groups(epdlb_batch* b) {
+  std::vector<epdlb_ctx*> order = b->groups;
+  std::stable_sort(order.begin(), order.end(),
+                   [](const epdlb_ctx* x, const epdlb_ctx* y) { return group_cost(x) > group_cost(y); });
+  std::vector<double> load(b->lanes.size(), 0.0);
+  for (auto* c : order) {
+    const size_t l = size_t(std::min_element(load.begin(), load.end()) - load.begin());
+    c->stream = b->lanes[l];
+    load[l] += group_cost(c);
+  }
+}
+
+// n steps of every group on the lanes, after the work queued on the batch stream
+// and before what is queued on it next.
+int batch_steps(epdlb_batch* b, int64_t n) {
+  if (!b->ev_fork) HIPCHK(hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming));
+  while (b->ev_join.size() < b->lanes.size()) {
+    hipEvent_t e;
+    HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    b->ev_join.push_back(e);
+  }
+  // every graph is there before any group advances (two steps keep the parity)
+  hipGraphExec_t g;
+  for (auto* c : b->groups) {
+    if (n >= 2) CHK(get_graph(c, 2, 0, &g));
+    if (n % 2) CHK(get_graph(c, 1, 0, &g));
+  }
+  HIPCHK(hipEventRecord(b->ev_fork, b->stream));
+  for (auto l : b->lanes)
+    if (l != b->stream) HIPCHK(hipStreamWaitEvent(l, b->ev_fork, 0));
   int r = EPDLB_OK;
-  if (hipEventRecord(b->ev_fork, b->cap) != hipSuccess) r = fail(EPDLB_EHIP, "fork event");
-  for (size_t i = 0; i < G && r == EPDLB_OK; ++i) {
-    epdlb_ctx* c = b->groups[i];
-    if (hipStreamWaitEvent(b->fork[i], b->ev_fork, 0) != hipSuccess) r = fail(EPDLB_EHIP, "fork wait");
-    for (int st = 0; st < steps && r == EPDLB_OK; ++st) {
-      r = run_advect_densities(c);
-      if (r == EPDLB_OK) r = run_force_lb(c);
+  for (; n > 0 && r == EPDLB_OK; n -= 2) {
+    const int k = n >= 2 ? 2 : 1;
+    for (auto* c : b->groups) {
+      r = get_graph(c, k, 0, &g);
+      if (r == EPDLB_OK && hipGraphLaunch(g, c->stream) != hipSuccess) r = fail(EPDLB_EHIP, "hipGraphLaunch failed");
+      if (r != EPDLB_OK) break;
+      if (k == 1) {
+        c->cur = 1 - c->cur;
+        c->fcur = 1 - c->fcur;
+      }
+      c->nstep += k;
     }
-    if (r == EPDLB_OK && hipEventRecord(b->ev_join[i], b->fork[i]) != hipSuccess) r = fail(EPDLB_EHIP, "join");
-    if (r == EPDLB_OK && hipStreamWaitEvent(b->cap, b->ev_join[i], 0) != hipSuccess)
-      r = fail(EPDLB_EHIP, "join wait");
+    b->nstep += k;
   }
-  hipGraph_t graph = nullptr;
-  const hipError_t e = hipStreamEndCapture(b->cap, &graph);
-  for (size_t i = 0; i < G; ++i) {
-    b->groups[i]->stream = own[i];
-    b->groups[i]->cur = cur0[i];
-    b->groups[i]->fcur = fcur0[i];
+  for (size_t l = 0; l < b->lanes.size(); ++l) {
+    if (b->lanes[l] == b->stream) continue;
+    HIPCHK(hipEventRecord(b->ev_join[l], b->lanes[l]));
+    HIPCHK(hipStreamWaitEvent(b->stream, b->ev_join[l], 0));
   }
-  if (r != EPDLB_OK) {
-    if (graph) (void)hipGraphDestroy(graph);
-    return r;
-  }
-  HIPCHK(e);
-  hipGraphExec_t exec = nullptr;
-  const hipError_t e2 = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-  (void)hipGraphDestroy(graph);
-  HIPCHK(e2);
-  b->graphs.push_back({steps, exec});
-  *out = exec;
-  return EPDLB_OK;
+  return r;
 }
 
 int batch_replica(epdlb_batch* b, int32_t r, epdlb_ctx** c, int* idx) {
@@ -2689,17 +2707,27 @@ int epdlb_batch_create(const epdlb_params* params, int32_t n_replicas, int devic
     b->where[r] = {int(g), int(members[g].size())};
     members[g].push_back(r);
   }
+  const int lc = make_lanes(b, shapes.size());
+  if (lc != EPDLB_OK) {
+    epdlb_batch_destroy(b);
+    return lc;
+  }
   for (size_t g = 0; g < shapes.size(); ++g) {
     std::vector<epdlb_params> rp;
     for (int r : members[g]) rp.push_back(params[r]);
     epdlb_ctx* c = nullptr;
-    const int rc = make_group(rp, device, &c);
+    const int rc = make_group(rp, device, b->lanes[0], &c);
     if (rc != EPDLB_OK) {
       epdlb_batch_destroy(b);
       return rc;
     }
     b->groups.push_back(c);
   }
+  if (hipStreamSynchronize(b->lanes[0]) != hipSuccess) {
+    epdlb_batch_destroy(b);
+    return fail(EPDLB_EHIP, "laying out the replica groups failed");
+  }
+  spread_groups(b);
   *out = b;
   return EPDLB_OK;
 }
@@ -2758,27 +2786,9 @@ int epdlb_batch_step(epdlb_batch* b, int64_t n) {
       }
       ++b->nstep;
     }
-    drop_batch_graphs(b);  // parities may have changed
     return EPDLB_OK;
   }
-  // the graphs' branches start after work already queued on the batch stream
-  while (n > 0) {
-    const int k = n >= 2 ? 2 : 1;
-    hipGraphExec_t g;
-    CHK(batch_graph(b, k, &g));
-    HIPCHK(hipGraphLaunch(g, b->stream));
-    if (k == 1) {
-      for (auto* c : b->groups) {
-        c->cur = 1 - c->cur;
-        c->fcur = 1 - c->fcur;
-      }
-      drop_batch_graphs(b);  // parities changed: recapture from the new state
-    }
-    for (auto* c : b->groups) c->nstep += k;
-    b->nstep += k;
-    n -= k;
-  }
-  return EPDLB_OK;
+  return n > 0 ? batch_steps(b, n) : EPDLB_OK;
 }
 
 int epdlb_batch_sync(epdlb_batch* b) {
@@ -2849,7 +2859,6 @@ int epdlb_batch_autotune(epdlb_batch* b, int32_t reps, const char* cache_path) {
   if (!b) return fail(EPDLB_EINVAL, "batch is NULL");
   HIPCHK(hipStreamSynchronize(b->stream));
   for (auto* c : b->groups) CHK(epdlb_autotune(c, reps, cache_path));
-  drop_batch_graphs(b);
   return EPDLB_OK;
 }
 
@@ -2901,12 +2910,11 @@ int epdlb_batch_info(epdlb_batch* b, int32_t* n_groups, int64_t* sites) {
 void epdlb_batch_destroy(epdlb_batch* b) {
   if (!b) return;
   if (b->stream) (void)hipStreamSynchronize(b->stream);
-  drop_batch_graphs(b);
   for (auto* c : b->groups) epdlb_destroy(c);
-  for (auto s : b->fork) (void)hipStreamDestroy(s);
+  for (auto l : b->lanes)
+    if (l != b->stream) (void)hipStreamDestroy(l);
   for (auto e : b->ev_join) (void)hipEventDestroy(e);
   if (b->ev_fork) (void)hipEventDestroy(b->ev_fork);
-  if (b->cap) (void)hipStreamDestroy(b->cap);
   if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
   delete b;
 }
