@@ -389,8 +389,9 @@ void epdlb_destroy(epdlb_ctx* ctx);
  * parameter set, Sec. IV) advanced together: replicas may differ in grid
  * (nx, ny), drive g and A fraction f_A, and must agree in every other model
  * parameter.  Replicas of one grid shape and A fraction share every kernel
- * launch; one captured graph advances all of them per step pair.  Replica indices follow
- * the order of `params`.
+ * launch; groups replay captured graphs side by side on streams of their own, after
+ * the work queued on the batch stream and before what is queued on it next.  Replica
+ * indices follow the order of `params`.
  * ------------------------------------------------------------------------- */
 typedef struct epdlb_batch epdlb_batch;
 
