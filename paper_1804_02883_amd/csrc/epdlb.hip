@@ -371,10 +371,11 @@ hipError_t launch_prop_row_r(const PropArgs<T>& a, hipStream_t s) {
   if constexpr (fft_ok<T, L, R>()) {
     using V = LdsView<T, L, R, true, 1>;
     const size_t lds = 2 * size_t(V::size_elems(a.nf)) * sizeof(T);
-    hipError_t e = prep_lds(k_prop_row<T, L, R, FIRST>, lds);
+    auto k = R == 8 && a.plain ? k_prop_row<T, L, R, FIRST, R != 8> : k_prop_row<T, L, R, FIRST, true>;
+    hipError_t e = prep_lds(k, lds);
     if (e != hipSuccess) return e;
     const int tiles = (a.ny / 2 + a.nf - 1) / a.nf;
-    launch_k((k_prop_row<T, L, R, FIRST>), dim3(tiles, 2, a.nrep), dim3(a.nf * (L / R)), lds, s, a);
+    launch_k(k, dim3(tiles, 2, a.nrep), dim3(a.nf * (L / R)), lds, s, a);
     return hipGetLastError();
   }
   return hipErrorInvalidValue;
@@ -402,10 +403,11 @@ hipError_t launch_prop_col_rn(const PropArgs<T>& a, hipStream_t s) {
   if constexpr (fft_ok<T, L, R>() && NF * (L / R) <= kMaxColThreads && (sizeof(T) == 4 || NF == 4)) {
     const size_t elems = col_mapped<L, R>() ? NF * ColView<T, L, R>::kLen : LdsView<T, L, R, false, NF>::size_elems(NF);
     const size_t lds = elems * sizeof(T2<T>);
-    hipError_t e = prep_lds(k_prop_col<T, L, R, NF>, lds);
+    auto k = R == 8 && a.plain ? k_prop_col<T, L, R, NF, R != 8> : k_prop_col<T, L, R, NF, true>;
+    hipError_t e = prep_lds(k, lds);
     if (e != hipSuccess) return e;
     const int tiles = (a.nx / 2 + NF - 1) / NF;
-    launch_k((k_prop_col<T, L, R, NF>), dim3(tiles, 2, a.nrep), dim3(NF * (L / R)), lds, s, a);
+    launch_k(k, dim3(tiles, 2, a.nrep), dim3(NF * (L / R)), lds, s, a);
     return hipGetLastError();
   }
   return hipErrorInvalidValue;
@@ -657,7 +659,10 @@ constexpr int res_cycles(int nx, int ny, int precision) {
   const int kx = nx / 16, ky = ny / 16;
   return (ky * kx + ky * ky) * 4 * (precision == 0 ? 64 : 32) * (kx > 4 ? (kx + 3) / 4 : 1);
 }
-bool resident(const epdlb_params& p) { return res_cycles(p.nx, p.ny, p.precision) <= kResMaxCycles; }
+bool resident(const epdlb_params& p) {
+  // not in surrogate runs, whose exact steps keep the passes' last bits (see make_prop_args)
+  return p.density_mode != 1 && res_cycles(p.nx, p.ny, p.precision) <= kResMaxCycles;
+}
 
 template <typename T, int LX, int LY> hipError_t launch_prop_res(const ResArgs<T>& a, int nrep, hipStream_t s) {
   if constexpr (res_cycles(LX, LY, sizeof(T) == 8 ? 0 : 1) <= kResMaxCycles) {
@@ -734,6 +739,9 @@ PropArgs<T> make_prop_args(epdlb_ctx* c) {
   a.a = 0;
   a.second = a.last = 0;
   a.frac[0] = a.frac[1] = a.fracJ = T(1);
+  // surrogate runs keep the plain form: the network's BF16 inputs see the last bits
+  // of an exact step, and its weights were made with that form
+  a.plain = p.density_mode == 1;
   a.nf = 1;
   a.nrep = c->nrep;
   a.rs = long(c->rstride);
