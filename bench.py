@@ -67,7 +67,20 @@ NN_FLOPS_PER_SITE = {"nn_conv0": 9 * 5 * 64 * 2, "nn_conv": 9 * 64 * 64 * 2}
 # WRITE x1.0); the summaries with their commands are under profiles/.  An
 # entry holds only while the sources its kernels are built from hash to
 # `source_sha256`; otherwise the bench reports null.
+_PROP_FILES = ("fft.hpp", "kernels.hpp")
+_NN_FILES = ("kernels.hpp", "nn.hpp")
 MEASURED_TRAFFIC = {
+    # profiles/prop_cfg3_traffic.md: the propagator passes on 1024 x 512, N = 64
+    ("cfg3", "prop_row"): dict(bytes_per_launch=16144386, files=_PROP_FILES,
+                               source_sha256="c1a466e0e5ec507ba2d38df66df3c58fe9f9449bf30371f8f15454f57d2537df"),
+    ("cfg3", "prop_col"): dict(bytes_per_launch=17092814, files=_PROP_FILES,
+                               source_sha256="c1a466e0e5ec507ba2d38df66df3c58fe9f9449bf30371f8f15454f57d2537df"),
+    # profiles/nn_conv_cfg5q_traffic.md: mean over the two 64 -> 64 launches of a surrogate step
+    ("cfg5q", "nn_conv"): dict(bytes_per_launch=63860198, files=_NN_FILES,
+                               source_sha256="0617045f6bec06fcecaf388874cae5920ec7c3e8f3b1c4707ae54f5a9857c131"),
+    # profiles/epd3_densities_256_traffic.md: mean over the passes of an evaluation
+    ("densities3d_256_N32", "p3_fft"): dict(bytes_per_launch=408023820, files=("epd3.hpp",),
+                                            source_sha256="08989653e1ee008741bed3175437b1bfc996838bd5780e9d1dd7840f7c5083fb"),
     # profiles/lb3_fluid3d_256_traffic.md: the step kernel without moment stores
     ("fluid3d_256", "lb3"): dict(bytes_per_launch=2751540306, files=("lb3.hpp",),
                                  source_sha256="00612d3692132a490494ae8af15af4cd91f576f0cf2aeadfdd24c455de263e97"),

@@ -2654,10 +2654,10 @@ int epdlb_profile_read(epdlb_ctx* c, epdlb_kernel_stat* out, int32_t cap, int32_
 
 void epdlb_destroy(epdlb_ctx* c) {
   if (!c) return;
+  if (c->stream) (void)hipStreamSynchronize(c->stream);  // graphs may be in flight
   drop_graphs(c);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
   for (hipEvent_t e : c->prof_ev) (void)hipEventDestroy(e);
-  if (c->stream) (void)hipStreamSynchronize(c->stream);
   if (c->own_mem && c->base) (void)hipFree(c->base);
   if (c->obs) (void)hipFree(c->obs);
   if (c->cg) (void)hipFree(c->cg);
