@@ -31,14 +31,35 @@ constexpr int kStageSlots = 16;
 constexpr int kStageMaxThreads = 8;
 constexpr size_t kStageIdle = 2;
 
+// The thread's current device while it lives; the one before is put back.
+class DeviceScope {
+ public:
+  explicit DeviceScope(int device) {
+    if (hipGetDevice(&before_) != hipSuccess) return;
+    set_ = device != before_ && hipSetDevice(device) == hipSuccess;
+  }
+  ~DeviceScope() {
+    if (set_) (void)hipSetDevice(before_);
+  }
+  DeviceScope(const DeviceScope&) = delete;
+  DeviceScope& operator=(const DeviceScope&) = delete;
+
+ private:
+  int before_ = 0;
+  bool set_ = false;
+};
+
 struct HostStage {
   int device = 0;
   unsigned char* pin = nullptr;
   hipEvent_t ev[kStageSlots] = {};
 
-  // false (and nothing held) when the pinned ring or an event cannot be had
+  // false (and nothing held) when the pinned ring or an event cannot be had.
+  // The events are made on the ring's device, whichever the caller's current one
+  // is: an event is recorded only on streams of its own device.
   bool ensure() {
     if (pin) return true;
+    const DeviceScope on(device);
     void* p = nullptr;
     if (hipHostMalloc(&p, kStageSlotBytes * kStageSlots, hipHostMallocDefault) != hipSuccess) {
       (void)hipGetLastError();
@@ -125,13 +146,20 @@ struct StageUser {
   StageUser& operator=(const StageUser&) = delete;
 };
 // One transfer's ring.  A transfer that failed may leave copies in flight into
-// it: the stream is waited for before another transfer gets the ring.
+// it: the stream is waited for, and no other transfer gets the ring.
 struct StageLease {
   HostStage st;
   hipStream_t s;
+  bool bad = false;
   StageLease(int device, hipStream_t stream) : st(StagePool::get().take(device)), s(stream) {}
-  ~StageLease() { StagePool::get().give(st); }
+  ~StageLease() {
+    if (bad)
+      st.release();
+    else
+      StagePool::get().give(st);
+  }
   hipError_t failed(hipError_t e) {
+    bad = true;
     (void)hipStreamSynchronize(s);
     return e;
   }

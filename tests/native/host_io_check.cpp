@@ -1,0 +1,89 @@
+// Checks of host_io.hpp against the runtime of hip/hip_runtime.h beside this
+// file.  One argument: the check's name.  Exit status 0: it holds.
+#include <cstdio>
+#include <string>
+#include <vector>
+
+#include "host_io.hpp"
+
+using namespace epdlb;
+
+#define REQUIRE(x)                                    \
+  do {                                                \
+    if (!(x)) {                                       \
+      std::printf("line %d: %s\n", __LINE__, #x);     \
+      return 1;                                       \
+    }                                                 \
+  } while (0)
+
+namespace {
+
+double value(size_t i, int seed) { return double((i * 2654435761u + unsigned(seed) * 40503u) % 16777213u); }
+
+template <typename T> hipError_t down(int device, MockStream& s, size_t count, int seed, bool* right) {
+  std::vector<T> dev(count);
+  for (size_t i = 0; i < count; ++i) dev[i] = T(value(i, seed));
+  std::vector<double> out(count, -1.0);
+  bool done = false;
+  const hipError_t e = staged_download(device, &s, out.data(), dev.data(), count, [](size_t, T v) { return double(v); }, &done);
+  *right = done;
+  for (size_t i = 0; i < count && *right; ++i) *right = out[i] == value(i, seed);
+  return e;
+}
+template <typename T> hipError_t up(int device, MockStream& s, size_t count, int seed, bool* right) {
+  std::vector<double> src(count);
+  for (size_t i = 0; i < count; ++i) src[i] = value(i, seed);
+  std::vector<T> dev(count, T(-1));
+  bool done = false, finite = false;
+  const hipError_t e = staged_upload(device, &s, dev.data(), src.data(), count, [](size_t, double v) { return T(v); }, &finite, &done);
+  *right = done && finite;
+  for (size_t i = 0; i < count && *right; ++i) *right = dev[i] == T(value(i, seed));
+  return e;
+}
+
+// A context's device is not the thread's current one.
+int other_device_current() {
+  StageUser a, b;
+  MockStream s0, s1;
+  s1.device = 1;
+  const size_t n = 2 * kStageMin + 77;
+  bool ok = false;
+  hipSetDevice(1);
+  REQUIRE(down<float>(0, s0, n, 1, &ok) == hipSuccess && ok);
+  REQUIRE(mock().device == 1);
+  REQUIRE(up<float>(0, s0, n, 2, &ok) == hipSuccess && ok);
+  REQUIRE(down<float>(1, s1, n, 3, &ok) == hipSuccess && ok);
+  hipSetDevice(0);
+  REQUIRE(up<double>(1, s1, n, 4, &ok) == hipSuccess && ok);
+  REQUIRE(down<double>(0, s0, n, 5, &ok) == hipSuccess && ok);
+  REQUIRE(mock().device == 0 && mock().pins == 2);
+  return 0;
+}
+
+// A transfer that fails gives its ring back to the system, not to the next one.
+int failed_transfer() {
+  StageUser a;
+  MockStream s;
+  bool ok = false;
+  mock().fail_record = 3;
+  REQUIRE(down<float>(0, s, 4 * kStageMin, 1, &ok) == hipErrorInvalidHandle);
+  REQUIRE(mock().pins == 1 && mock().freed == 1);
+  REQUIRE(down<float>(0, s, 4 * kStageMin, 2, &ok) == hipSuccess && ok);
+  REQUIRE(mock().pins == 2 && mock().freed == 1);
+  mock().fail_record = mock().records + 3;
+  REQUIRE(up<float>(0, s, 4 * kStageMin, 1, &ok) == hipErrorInvalidHandle);
+  REQUIRE(mock().freed == 2);
+  REQUIRE(up<float>(0, s, 4 * kStageMin, 2, &ok) == hipSuccess && ok);
+  REQUIRE(mock().pins == 3);
+  return 0;
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::string what = argc > 1 ? argv[1] : "";
+  if (what == "other_device_current") return other_device_current();
+  if (what == "failed_transfer") return failed_transfer();
+  std::printf("no check of that name\n");
+  return 2;
+}
