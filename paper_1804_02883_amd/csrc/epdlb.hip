@@ -365,13 +365,17 @@ constexpr bool fft_ok() {
   return (R == 8 || R == 4 || ((R == 16 || R == 2) && sizeof(T) == 4)) && L >= R;
 }
 constexpr int kMaxColThreads = 512;
+// Shapes whose passes come with the plain convolution too (surrogate runs): FP32 at
+// every R, FP64 at the R = 8 that such runs keep.
+template <typename T, int R> constexpr bool plain_ok() { return sizeof(T) == 4 || R == 8; }
 
 template <typename T, int L, int R, bool FIRST>
 hipError_t launch_prop_row_r(const PropArgs<T>& a, hipStream_t s) {
   if constexpr (fft_ok<T, L, R>()) {
     using V = LdsView<T, L, R, true, 1>;
     const size_t lds = 2 * size_t(V::size_elems(a.nf)) * sizeof(T);
-    auto k = R == 8 && a.plain ? k_prop_row<T, L, R, FIRST, R != 8> : k_prop_row<T, L, R, FIRST, true>;
+    if (a.plain && !plain_ok<T, R>()) return hipErrorInvalidValue;
+    auto k = a.plain ? k_prop_row<T, L, R, FIRST, !plain_ok<T, R>()> : k_prop_row<T, L, R, FIRST, true>;
     hipError_t e = prep_lds(k, lds);
     if (e != hipSuccess) return e;
     const int tiles = (a.ny / 2 + a.nf - 1) / a.nf;
@@ -389,12 +393,17 @@ hipError_t launch_prop_row(const PropArgs<T>& a, int R, hipStream_t s) {
   }
   return launch_prop_row_r<T, L, 8, false>(a, s);
 }
-// The first pass of a propagation; it comes with R = 4 and 8.
+// The first pass of a propagation.  It comes with R = 4 and 8; in surrogate runs,
+// where every pass rounds as the others do, with every R.
 template <typename T, int L>
 hipError_t launch_prop_first(const PropArgs<T>& a, int R, hipStream_t s) {
   PropArgs<T> f = a;
-  const int r = R >= 8 ? 8 : 4;
+  const int r = a.plain ? R : (R >= 8 ? 8 : 4);
   f.nf = clampi(64 * r / L, 1, a.ny / 2);
+  if constexpr (sizeof(T) == 4) {
+    if (r == 16) return launch_prop_row_r<T, L, 16, true>(f, s);
+    if (r == 2) return launch_prop_row_r<T, L, 2, true>(f, s);
+  }
   return r == 8 ? launch_prop_row_r<T, L, 8, true>(f, s) : launch_prop_row_r<T, L, 4, true>(f, s);
 }
 
@@ -403,7 +412,8 @@ hipError_t launch_prop_col_rn(const PropArgs<T>& a, hipStream_t s) {
   if constexpr (fft_ok<T, L, R>() && NF * (L / R) <= kMaxColThreads && (sizeof(T) == 4 || NF == 4)) {
     const size_t elems = col_mapped<L, R>() ? NF * ColView<T, L, R>::kLen : LdsView<T, L, R, false, NF>::size_elems(NF);
     const size_t lds = elems * sizeof(T2<T>);
-    auto k = R == 8 && a.plain ? k_prop_col<T, L, R, NF, R != 8> : k_prop_col<T, L, R, NF, true>;
+    if (a.plain && !plain_ok<T, R>()) return hipErrorInvalidValue;
+    auto k = a.plain ? k_prop_col<T, L, R, NF, !plain_ok<T, R>()> : k_prop_col<T, L, R, NF, true>;
     hipError_t e = prep_lds(k, lds);
     if (e != hipSuccess) return e;
     const int tiles = (a.nx / 2 + NF - 1) / NF;
@@ -1261,6 +1271,8 @@ hipError_t launch_family(epdlb_ctx* c, int fam, int R, int nf, hipStream_t s) {
 // Average microseconds per launch of one candidate, or a negative value if the
 // candidate cannot be launched.
 double time_candidate(epdlb_ctx* c, int fam, int R, int nf, int reps) {
+  // FP64 surrogate runs keep R = 8 in every pass (see default_shapes)
+  if (c->p.density_mode == 1 && c->p.precision == 0 && R != 8) return -1.0;
   auto launch = [&](hipStream_t s) {
     return c->p.precision == 0 ? launch_family<double>(c, fam, R, nf, s)
                                : launch_family<float>(c, fam, R, nf, s);
@@ -1560,9 +1572,10 @@ int get_graph(epdlb_ctx* c, int steps, int kind, hipGraphExec_t* out) {
 // 3.5, columns 6.2 -> 4.8; 1024 x 512 rows 8.7 -> 7.7, columns 8.8 -> 8.2; 512 x 512
 // rows 5.6 -> 5.2, columns 8.2 -> 6.8; 128 x 128 4.8 -> 3.4 and 5.1 -> 4.0; FP64
 // 256 x 128 8.1 -> 4.0 and 5.1 -> 4.5.
-// A surrogate context keeps R = 8: its network reads the potentials rounded to
-// BF16, so a transform that rounds differently moves whole BF16 steps and a run
-// would not repeat (2.6e-5 of the potentials after 50 steps of 512 x 512).
+// A surrogate context starts at R = 8, and its passes take the plain convolution at
+// every R: its network reads the potentials rounded to BF16, so where a transform
+// rounds differently whole BF16 steps move (2.6e-5 of the potentials after 50 steps
+// of 512 x 512) and runs would no longer match the ones made before.
 void default_shapes(epdlb_ctx* c) {
   const epdlb_params* p = &c->p;
   const bool keep = p->density_mode == 1;
