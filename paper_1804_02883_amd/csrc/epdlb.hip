@@ -57,32 +57,6 @@ int fail(int code, const std::string& msg) {
     if (r_ != EPDLB_OK) return r_; \
   } while (0)
 
-// Host FP64 values -> device planes of T, each through conv(index, value);
-// returns when the host array is free again.
-template <typename T, class Conv>
-int host_upload(int device, hipStream_t s, T* dst, const double* src, size_t count, Conv conv) {
-  bool done = false, finite = true;
-  if (count >= kStageMin) HIPCHK(staged_upload(device, s, dst, src, count, conv, &finite, &done));
-  if (done) return EPDLB_OK;
-  std::vector<T> h(count);
-  for (size_t i = 0; i < count; ++i) h[i] = conv(i, src[i]);
-  HIPCHK(hipMemcpyAsync(dst, h.data(), count * sizeof(T), hipMemcpyHostToDevice, s));
-  HIPCHK(hipStreamSynchronize(s));
-  return EPDLB_OK;
-}
-// Device planes of T -> host FP64 values through conv(index, value).
-template <typename T, class Conv>
-int host_download(int device, hipStream_t s, double* dst, const T* src, size_t count, Conv conv) {
-  bool done = false;
-  if (count >= kStageMin) HIPCHK(staged_download(device, s, dst, src, count, conv, &done));
-  if (done) return EPDLB_OK;
-  std::vector<T> h(count);
-  HIPCHK(hipMemcpyAsync(h.data(), src, count * sizeof(T), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
-  for (size_t i = 0; i < count; ++i) dst[i] = conv(i, h[i]);
-  return EPDLB_OK;
-}
-
 bool is_pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 
 // ---------------------------------------------------------------------------
@@ -1333,14 +1307,16 @@ std::string tune_key(const epdlb_ctx* c, int fam) {
 // ---------------------------------------------------------------------------
 template <typename T>
 int upload_t(epdlb_ctx* c, size_t off, const double* src, size_t count) {
-  return host_upload(c->device, c->stream, c->ptr<T>(off), src, count, [](size_t, double v) { return T(v); });
+  HIPCHK(host_upload(c->device, c->stream, c->ptr<T>(off), src, count, AsIs()));
+  return EPDLB_OK;
 }
 int upload(epdlb_ctx* c, size_t off, const double* src, size_t count) {
   return c->p.precision == 0 ? upload_t<double>(c, off, src, count) : upload_t<float>(c, off, src, count);
 }
 template <typename T>
 int download_t(epdlb_ctx* c, size_t off, double* dst, size_t count) {
-  return host_download(c->device, c->stream, dst, c->ptr<const T>(off), count, [](size_t, T v) { return double(v); });
+  HIPCHK(host_download(c->device, c->stream, dst, c->ptr<const T>(off), count, AsIs()));
+  return EPDLB_OK;
 }
 int download(epdlb_ctx* c, size_t off, double* dst, size_t count) {
   return c->p.precision == 0 ? download_t<double>(c, off, dst, count) : download_t<float>(c, off, dst, count);
@@ -1448,8 +1424,9 @@ const double kW9[9] = {4.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 36, 1.
 template <typename T> int upload_populations_t(epdlb_ctx* c, size_t off, const double* f) {
   const size_t n = size_t(c->p.nx) * c->p.ny;
   const int log2n = __builtin_ctzll(n);  // both sides are powers of two
-  return host_upload(c->device, c->stream, c->ptr<T>(off), f, 9 * n,
-                     [=](size_t i, double v) { return T(v - kW9[i >> log2n]); });
+  HIPCHK(host_upload(c->device, c->stream, c->ptr<T>(off), f, 9 * n,
+                     [=](size_t i, double v) { return v - kW9[i >> log2n]; }));
+  return EPDLB_OK;
 }
 int upload_populations(epdlb_ctx* c, size_t off, const double* f) {
   return c->p.precision == 0 ? upload_populations_t<double>(c, off, f) : upload_populations_t<float>(c, off, f);
@@ -3355,9 +3332,11 @@ int lb3_steps(epdlb_lb3* c, int64_t n, hipEvent_t* ev) {
 template <typename T>
 int lb3_upload_t(epdlb_lb3* c, void* dst, const double* src, size_t count, const double* minus_w) {
   T* d = static_cast<T*>(dst);
-  if (!minus_w) return host_upload(c->device, c->stream, d, src, count, [](size_t, double v) { return T(v); });
   const size_t n = size_t(c->n);
-  return host_upload(c->device, c->stream, d, src, count, [=](size_t i, double v) { return T(v - minus_w[i / n]); });
+  HIPCHK(minus_w ? host_upload(c->device, c->stream, d, src, count,
+                               [=](size_t i, double v) { return v - minus_w[i / n]; })
+                 : host_upload(c->device, c->stream, d, src, count, AsIs()));
+  return EPDLB_OK;
 }
 int lb3_upload(epdlb_lb3* c, void* dst, const double* src, size_t count, const double* minus_w) {
   return c->precision ? lb3_upload_t<float>(c, dst, src, count, minus_w)
@@ -3367,9 +3346,11 @@ int lb3_upload(epdlb_lb3* c, void* dst, const double* src, size_t count, const d
 template <typename T>
 int lb3_download_t(epdlb_lb3* c, double* dst, const void* src, size_t count, const double* plus_w) {
   const T* p = static_cast<const T*>(src);
-  if (!plus_w) return host_download(c->device, c->stream, dst, p, count, [](size_t, T v) { return double(v); });
   const size_t n = size_t(c->n);
-  return host_download(c->device, c->stream, dst, p, count, [=](size_t i, T v) { return plus_w[i / n] + double(v); });
+  HIPCHK(plus_w ? host_download(c->device, c->stream, dst, p, count,
+                                [=](size_t i, T v) { return plus_w[i / n] + double(v); })
+                : host_download(c->device, c->stream, dst, p, count, AsIs()));
+  return EPDLB_OK;
 }
 int lb3_download(epdlb_lb3* c, double* dst, const void* src, size_t count, const double* plus_w) {
   return c->precision ? lb3_download_t<float>(c, dst, src, count, plus_w)
@@ -3920,16 +3901,16 @@ namespace {
 // context's potentials.
 template <typename T> int epd3_call(epdlb_epd3* c, const double* omega, double* phi) {
   const size_t count = 3 * size_t(c->n);
-  auto in = [](size_t, double v) { return T(v); };
   bool done = false, finite = true;
-  if (count >= kStageMin) HIPCHK(staged_upload(c->device, c->stream, static_cast<T*>(c->phi), omega, count, in, &finite, &done));
+  if (count >= kStageMin)
+    HIPCHK(staged_upload(c->device, c->stream, static_cast<T*>(c->phi), omega, count, AsIs(), &finite, &done));
   if (done && finite) std::swap(c->w, c->phi);
   if (!done) finite = all_finite(omega, count);
   if (!finite) return fail(EPDLB_EINVAL, "non-finite potential");
-  if (!done) CHK(host_upload(c->device, c->stream, static_cast<T*>(c->w), omega, count, in));
+  if (!done) HIPCHK(host_upload(c->device, c->stream, static_cast<T*>(c->w), omega, count, AsIs()));
   CHK(p3_densities<T>(c));
-  return host_download(c->device, c->stream, phi, static_cast<const T*>(c->phi), count,
-                       [](size_t, T v) { return double(v); });
+  HIPCHK(host_download(c->device, c->stream, phi, static_cast<const T*>(c->phi), count, AsIs()));
+  return EPDLB_OK;
 }
 
 }  // namespace

@@ -21,6 +21,7 @@
 #include <cmath>
 #include <mutex>
 #include <thread>
+#include <type_traits>
 #include <vector>
 
 namespace epdlb {
@@ -232,7 +233,7 @@ hipError_t staged_download(int device, hipStream_t s, double* dst, const T* src,
       }
       const T* h = reinterpret_cast<const T*>(st.pin + size_t(c % kStageSlots) * kStageSlotBytes);
       const size_t i0 = size_t(c) * per, i1 = std::min(count, i0 + per);
-      for (size_t i = i0; i < i1; ++i) dst[i] = conv(i, h[i - i0]);
+      for (size_t i = i0; i < i1; ++i) dst[i] = double(conv(i, h[i - i0]));
       busy[c % kStageSlots].store(0, std::memory_order_release);
     }
   });
@@ -291,7 +292,7 @@ hipError_t staged_upload(int device, hipStream_t s, T* dst, const double* src, s
       bool f = true;
       for (size_t i = i0; i < i1; ++i) {
         f &= std::isfinite(src[i]);
-        h[i - i0] = conv(i, src[i]);
+        h[i - i0] = T(conv(i, src[i]));
       }
       if (!f) fin.store(false, std::memory_order_relaxed);
       ready[c % kStageSlots].store(c, std::memory_order_release);
@@ -319,6 +320,58 @@ hipError_t staged_upload(int device, hipStream_t s, T* dst, const double* src, s
   }
   w.join();
   *finite = fin.load();
+  return hipSuccess;
+}
+
+// The conversion that leaves a value as it is but for its type.
+struct AsIs {
+  template <class X> X operator()(size_t, X v) const { return v; }
+};
+// FP64 planes take FP64 host arrays as they lie.
+template <typename T, class Conv> constexpr bool direct_copy() {
+  return std::is_same<T, double>::value && std::is_same<Conv, AsIs>::value;
+}
+
+// Host FP64 values -> device planes of T, each through conv(index, value);
+// returns when the host array is free again.
+template <typename T, class Conv>
+hipError_t host_upload(int device, hipStream_t s, T* dst, const double* src, size_t count, Conv conv) {
+  if (count >= kStageMin) {
+    bool done = false, finite = true;
+    const hipError_t e = staged_upload(device, s, dst, src, count, conv, &finite, &done);
+    if (e != hipSuccess || done) return e;
+  }
+  std::vector<T> h;
+  const void* from = src;
+  if constexpr (!direct_copy<T, Conv>()) {
+    h.resize(count);
+    for (size_t i = 0; i < count; ++i) h[i] = T(conv(i, src[i]));
+    from = h.data();
+  }
+  const hipError_t e = hipMemcpyAsync(dst, from, count * sizeof(T), hipMemcpyHostToDevice, s);
+  const hipError_t w = hipStreamSynchronize(s);
+  return e != hipSuccess ? e : w;
+}
+
+// Device planes of T -> host FP64 values through conv(index, value).
+template <typename T, class Conv>
+hipError_t host_download(int device, hipStream_t s, double* dst, const T* src, size_t count, Conv conv) {
+  if (count >= kStageMin) {
+    bool done = false;
+    const hipError_t e = staged_download(device, s, dst, src, count, conv, &done);
+    if (e != hipSuccess || done) return e;
+  }
+  std::vector<T> h;
+  void* to = dst;
+  if constexpr (!direct_copy<T, Conv>()) {
+    h.resize(count);
+    to = h.data();
+  }
+  const hipError_t e = hipMemcpyAsync(to, src, count * sizeof(T), hipMemcpyDeviceToHost, s);
+  const hipError_t w = hipStreamSynchronize(s);
+  if (e != hipSuccess || w != hipSuccess) return e != hipSuccess ? e : w;
+  if constexpr (!direct_copy<T, Conv>())
+    for (size_t i = 0; i < count; ++i) dst[i] = double(conv(i, h[i]));
   return hipSuccess;
 }
 

@@ -78,12 +78,38 @@ int failed_transfer() {
   return 0;
 }
 
+// FP64 planes and FP64 host arrays: below the ring's size the copies lie on the
+// caller's array; values that change on the way (a type, an offset) do not.
+int fp64_as_it_lies() {
+  StageUser a;
+  MockStream s;
+  const size_t n = 98304;  // 3 planes of 64 x 32 x 16
+  std::vector<double> src(n), dev(n, -1.0), out(n, -1.0);
+  for (size_t i = 0; i < n; ++i) src[i] = value(i, 7);
+  REQUIRE(host_upload(0, &s, dev.data(), src.data(), n, AsIs()) == hipSuccess);
+  REQUIRE(mock().host == src.data() && dev == src);
+  REQUIRE(host_download(0, &s, out.data(), static_cast<const double*>(dev.data()), n, AsIs()) == hipSuccess);
+  REQUIRE(mock().host == out.data() && out == src && mock().copies == 2);
+  REQUIRE(host_upload(0, &s, dev.data(), src.data(), n, [](size_t i, double v) { return v - double(i); }) == hipSuccess);
+  REQUIRE(dev[0] == src[0] && dev[n - 1] == src[n - 1] - double(n - 1));
+  REQUIRE(host_download(0, &s, out.data(), static_cast<const double*>(dev.data()), n,
+                        [](size_t i, double v) { return v + double(i); }) == hipSuccess);
+  REQUIRE(out == src);
+  std::vector<float> f(n, -1.0f);
+  REQUIRE(host_upload(0, &s, f.data(), src.data(), n, AsIs()) == hipSuccess);
+  std::vector<double> back(n, -1.0);
+  REQUIRE(host_download(0, &s, back.data(), static_cast<const float*>(f.data()), n, AsIs()) == hipSuccess);
+  REQUIRE(back == src && mock().pins == 0);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "other_device_current") return other_device_current();
   if (what == "failed_transfer") return failed_transfer();
+  if (what == "fp64_as_it_lies") return fp64_as_it_lies();
   std::printf("no check of that name\n");
   return 2;
 }
