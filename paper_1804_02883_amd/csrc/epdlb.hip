@@ -111,6 +111,7 @@ Layout make_layout(const epdlb_params& p) {
   L.rho = take(plane);
   L.u = take(2 * plane);
   L.boltz = take(2 * plane);
+  // mult_x to wnB: the constant tables, uploaded as one piece
   L.mult_x = take(size_t(p.nx) * es);
   L.mult_y = take(size_t(p.ny) * es);
   L.tw_x = take(size_t(p.nx) * 2 * es);
@@ -1374,36 +1375,41 @@ int upload_tables(epdlb_ctx* c) {
     }
     out[L / 2] += miss;
   };
-  std::vector<double> mx, my, tx, ty, kx, ky;
-  if (resident(p)) {
-    ker(p.nx, kx);
-    ker(p.ny, ky);
+  // node weights: trapezoid over each segment, split by its A fraction (one for the
+  // replicas of a group, which share every launch)
+  const std::vector<double> a = segment_fractions(p);
+  std::vector<double> wA(N + 1, 0.0), wB(N + 1, 0.0);
+  for (int j = 0; j < N; ++j) {
+    wA[j] += 0.5 * ds * a[j];
+    wA[j + 1] += 0.5 * ds * a[j];
+    wB[j] += 0.5 * ds * (1.0 - a[j]);
+    wB[j + 1] += 0.5 * ds * (1.0 - a[j]);
   }
-  mult(p.nx, mx);
-  mult(p.ny, my);
-  tw(p.nx, tx);
-  tw(p.ny, ty);
+  // The tables lie side by side, and a replica's go up in one copy: a copy of its own
+  // for each is 15-20 us, of which the resident grids' two more made a batch of 512
+  // replicas of 64 x 64 take 64 ms to create, 47 before they came.
+  const Layout& l = c->L;
+  std::vector<unsigned char> img(l.scal - l.mult_x, 0);
+  auto put = [&](size_t off, const std::vector<double>& v) {
+    unsigned char* d = img.data() + (off - l.mult_x);
+    if (p.precision == 0)
+      std::memcpy(d, v.data(), v.size() * sizeof(double));
+    else
+      for (size_t i = 0; i < v.size(); ++i) reinterpret_cast<float*>(d)[i] = float(v[i]);
+  };
+  std::vector<double> t;
+  mult(p.nx, t), put(l.mult_x, t);
+  mult(p.ny, t), put(l.mult_y, t);
+  tw(p.nx, t), put(l.tw_x, t);
+  tw(p.ny, t), put(l.tw_y, t);
+  if (resident(p)) {
+    ker(p.nx, t), put(l.ker_x, t);
+    ker(p.ny, t), put(l.ker_y, t);
+  }
+  put(l.wnA, wA);
+  put(l.wnB, wB);
   for (int r = 0; r < c->nrep; ++r) {
-    const size_t o = c->roff(r);
-    CHK(upload(c, o + c->L.mult_x, mx.data(), mx.size()));
-    CHK(upload(c, o + c->L.mult_y, my.data(), my.size()));
-    if (!kx.empty()) {
-      CHK(upload(c, o + c->L.ker_x, kx.data(), kx.size()));
-      CHK(upload(c, o + c->L.ker_y, ky.data(), ky.size()));
-    }
-    CHK(upload(c, o + c->L.tw_x, tx.data(), tx.size()));
-    CHK(upload(c, o + c->L.tw_y, ty.data(), ty.size()));
-    // node weights: trapezoid over each segment, split by its A fraction
-    const std::vector<double> a = segment_fractions(c->rp[r]);
-    std::vector<double> wA(N + 1, 0.0), wB(N + 1, 0.0);
-    for (int j = 0; j < N; ++j) {
-      wA[j] += 0.5 * ds * a[j];
-      wA[j + 1] += 0.5 * ds * a[j];
-      wB[j] += 0.5 * ds * (1.0 - a[j]);
-      wB[j + 1] += 0.5 * ds * (1.0 - a[j]);
-    }
-    CHK(upload(c, o + c->L.wnA, wA.data(), wA.size()));
-    CHK(upload(c, o + c->L.wnB, wB.data(), wB.size()));
+    HIPCHK(hipMemcpyAsync(c->base + c->roff(r) + l.mult_x, img.data(), img.size(), hipMemcpyHostToDevice, c->stream));
     CHK(reset_scal(c, r));
   }
   return EPDLB_OK;
@@ -3753,7 +3759,7 @@ template <typename T> int p3_densities(epdlb_epd3* c) {
 
 // Tables of axis ax: multipliers exp(-R_G^2 k^2 ds)/L, what their rounding to
 // T left, then the twiddles.
-template <typename T> int p3_tables(epdlb_epd3* c, int ax) {
+template <typename T> void p3_tables(const epdlb_epd3* c, int ax, unsigned char* out) {
   const int L = c->len[ax];
   std::vector<T> t(2 * size_t(L));
   for (int e = 0; e < L; ++e) {
@@ -3770,9 +3776,7 @@ template <typename T> int p3_tables(epdlb_epd3* c, int ax) {
     case 256: TwTables<T, 256, 8>::fill(t); break;
     case 512: TwTables<T, 512, 8>::fill(t); break;
   }
-  HIPCHK(hipMemcpyAsync(c->tab[ax], t.data(), t.size() * sizeof(T), hipMemcpyHostToDevice, c->stream));
-  HIPCHK(hipStreamSynchronize(c->stream));
-  return EPDLB_OK;
+  std::memcpy(out, t.data(), t.size() * sizeof(T));
 }
 
 }  // namespace
@@ -3859,15 +3863,25 @@ int epdlb_epd3_create(int32_t nx, int32_t ny, int32_t nz, int32_t n_contour, dou
   b += 2 * plane;
   c->E = b;
   b += 2 * plane;
+  // the tables and the node weights go up as one piece
+  unsigned char* const tables = b;
+  std::vector<unsigned char> img(3 * tab_bytes + nodes.size() * sizeof(double), 0);
   for (int ax = 0; ax < 3; ++ax) {
     c->tab[ax] = b;
     b += tab_bytes;
   }
+  for (int ax = 0; ax < c->ndim; ++ax) {
+    if (precision)
+      p3_tables<float>(c, ax, img.data() + ax * tab_bytes);
+    else
+      p3_tables<double>(c, ax, img.data() + ax * tab_bytes);
+  }
+  c->nodes = reinterpret_cast<double*>(b);
+  std::memcpy(img.data() + 3 * tab_bytes, nodes.data(), nodes.size() * sizeof(double));
+  b += align256(nodes.size() * sizeof(double));
   c->part = reinterpret_cast<double*>(b);
   b += part_bytes;
   c->sums = reinterpret_cast<double*>(b);
-  b += align256(8 * sizeof(double));
-  c->nodes = reinterpret_cast<double*>(b);
   if (stream) {
     c->stream = reinterpret_cast<hipStream_t>(stream);
   } else {
@@ -3877,18 +3891,10 @@ int epdlb_epd3_create(int32_t nx, int32_t ny, int32_t nz, int32_t n_contour, dou
     }
     c->own_stream = true;
   }
-  if (hipMemcpyAsync(c->nodes, nodes.data(), nodes.size() * sizeof(double), hipMemcpyHostToDevice, c->stream) !=
-          hipSuccess ||
+  if (hipMemcpyAsync(tables, img.data(), img.size(), hipMemcpyHostToDevice, c->stream) != hipSuccess ||
       hipStreamSynchronize(c->stream) != hipSuccess) {
     epdlb_epd3_destroy(c);
-    return fail(EPDLB_EHIP, "uploading the contour weights failed");
-  }
-  for (int ax = 0; ax < c->ndim; ++ax) {
-    const int r = precision ? p3_tables<float>(c, ax) : p3_tables<double>(c, ax);
-    if (r != EPDLB_OK) {
-      epdlb_epd3_destroy(c);
-      return r;
-    }
+    return fail(EPDLB_EHIP, "uploading the transform tables failed");
   }
   *out = c;
   return EPDLB_OK;
