@@ -1,7 +1,9 @@
 // Checks of host_io.hpp against the runtime of hip/hip_runtime.h beside this
 // file.  One argument: the check's name.  Exit status 0: it holds.
+#include <chrono>
 #include <cstdio>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "host_io.hpp"
@@ -20,12 +22,17 @@ namespace {
 
 double value(size_t i, int seed) { return double((i * 2654435761u + unsigned(seed) * 40503u) % 16777213u); }
 
+// The worker of the first chunk falls behind the others.
+void slow(size_t i) {
+  if (i == 0) std::this_thread::sleep_for(std::chrono::milliseconds(30));
+}
+
 template <typename T> hipError_t down(int device, MockStream& s, size_t count, int seed, bool* right) {
   std::vector<T> dev(count);
   for (size_t i = 0; i < count; ++i) dev[i] = T(value(i, seed));
   std::vector<double> out(count, -1.0);
   bool done = false;
-  const hipError_t e = staged_download(device, &s, out.data(), dev.data(), count, [](size_t, T v) { return double(v); }, &done);
+  const hipError_t e = staged_download(device, &s, out.data(), dev.data(), count, [](size_t i, T v) { return slow(i), double(v); }, &done);
   *right = done;
   for (size_t i = 0; i < count && *right; ++i) *right = out[i] == value(i, seed);
   return e;
@@ -35,7 +42,7 @@ template <typename T> hipError_t up(int device, MockStream& s, size_t count, int
   for (size_t i = 0; i < count; ++i) src[i] = value(i, seed);
   std::vector<T> dev(count, T(-1));
   bool done = false, finite = false;
-  const hipError_t e = staged_upload(device, &s, dev.data(), src.data(), count, [](size_t, double v) { return T(v); }, &finite, &done);
+  const hipError_t e = staged_upload(device, &s, dev.data(), src.data(), count, [](size_t i, double v) { return slow(i), T(v); }, &finite, &done);
   *right = done && finite;
   for (size_t i = 0; i < count && *right; ++i) *right = dev[i] == T(value(i, seed));
   return e;
@@ -103,6 +110,21 @@ int fp64_as_it_lies() {
   return 0;
 }
 
+// Every slot used several times, ragged and whole last chunks, the smallest sizes.
+template <typename T> int over_the_ring() {
+  StageUser a;
+  MockStream s;
+  const size_t ring = kStageSlotBytes / sizeof(T) * kStageSlots;
+  bool ok = false;
+  int seed = 0;
+  for (size_t n : {size_t(1), kStageMin, kStageMin + 1, ring, ring + 1, 3 * ring, 3 * ring + ring / 3 + 5}) {
+    REQUIRE(down<T>(0, s, n, ++seed, &ok) == hipSuccess && ok);
+    REQUIRE(up<T>(0, s, n, ++seed, &ok) == hipSuccess && ok);
+  }
+  REQUIRE(mock().pins == 1);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -110,6 +132,8 @@ int main(int argc, char** argv) {
   if (what == "other_device_current") return other_device_current();
   if (what == "failed_transfer") return failed_transfer();
   if (what == "fp64_as_it_lies") return fp64_as_it_lies();
+  if (what == "over_the_ring_fp32") return over_the_ring<float>();
+  if (what == "over_the_ring_fp64") return over_the_ring<double>();
   std::printf("no check of that name\n");
   return 2;
 }

@@ -19,7 +19,8 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["other_device_current", "failed_transfer", "fp64_as_it_lies"])
+@pytest.mark.parametrize("check", ["other_device_current", "failed_transfer", "fp64_as_it_lies",
+                                   "over_the_ring_fp32", "over_the_ring_fp64"])
 def test_host_io(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
