@@ -71,13 +71,13 @@ _PROP_FILES = ("fft.hpp", "kernels.hpp")
 _NN_FILES = ("kernels.hpp", "nn.hpp")
 MEASURED_TRAFFIC = {
     # profiles/prop_cfg3_traffic.md: the propagator passes on 1024 x 512, N = 64
-    ("cfg3", "prop_row"): dict(bytes_per_launch=16144386, files=_PROP_FILES,
-                               source_sha256="c1a466e0e5ec507ba2d38df66df3c58fe9f9449bf30371f8f15454f57d2537df"),
-    ("cfg3", "prop_col"): dict(bytes_per_launch=17092814, files=_PROP_FILES,
-                               source_sha256="c1a466e0e5ec507ba2d38df66df3c58fe9f9449bf30371f8f15454f57d2537df"),
+    ("cfg3", "prop_row"): dict(bytes_per_launch=16135474, files=_PROP_FILES,
+                               source_sha256="08bfc791d877eb1afbd7face5f329e76cf03ac61a63cc85f97a62aeb64baf22d"),
+    ("cfg3", "prop_col"): dict(bytes_per_launch=17106137, files=_PROP_FILES,
+                               source_sha256="08bfc791d877eb1afbd7face5f329e76cf03ac61a63cc85f97a62aeb64baf22d"),
     # profiles/nn_conv_cfg5q_traffic.md: mean over the two 64 -> 64 launches of a surrogate step
-    ("cfg5q", "nn_conv"): dict(bytes_per_launch=63860198, files=_NN_FILES,
-                               source_sha256="0617045f6bec06fcecaf388874cae5920ec7c3e8f3b1c4707ae54f5a9857c131"),
+    ("cfg5q", "nn_conv"): dict(bytes_per_launch=63860115, files=_NN_FILES,
+                               source_sha256="c8445d6bebc2e05a33c74b1f458fde418ced39a43cc11ddbbd4af27128355c1f"),
     # profiles/epd3_densities_256_traffic.md: mean over the passes of an evaluation
     ("densities3d_256_N32", "p3_fft"): dict(bytes_per_launch=408023820, files=("epd3.hpp",),
                                             source_sha256="08989653e1ee008741bed3175437b1bfc996838bd5780e9d1dd7840f7c5083fb"),

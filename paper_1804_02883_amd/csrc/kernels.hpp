@@ -162,7 +162,7 @@ template <typename T> struct PropArgs {
   int last;               // partial sums of q_N for Q_P
   T frac[2];              // first pass: A fraction of chain c's segment at step 0
   T fracJ;
-  bool plain;             // convolutions set no constant aside (see convolve); R = 8 only
+  bool plain;             // convolutions set no constant aside (see convolve)
   double* partials;       // last: per-block sums of q_N, chain c at [c*gridDim.x]
   int nf;                 // transforms per block (row kernels)
   int nrep;               // replicas in the launch (gridDim.z)
@@ -464,6 +464,7 @@ __global__ void __launch_bounds__(512) k_prop_col(PropArgs<T> P) {
 template <typename T> struct Mfma16;
 template <> struct Mfma16<float> {
   typedef float acc __attribute__((ext_vector_type(4)));
+  typedef float lds4 __attribute__((ext_vector_type(4), aligned(16)));  // four values of a row, as they lie in LDS
   static __device__ __forceinline__ acc mma(float a, float b, acc c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   }
@@ -472,6 +473,7 @@ template <> struct Mfma16<float> {
 };
 template <> struct Mfma16<double> {
   typedef double acc __attribute__((ext_vector_type(4)));
+  typedef double lds4 __attribute__((ext_vector_type(4), aligned(16)));  // two 16-byte reads (acc asks for 32-byte alignment)
   static __device__ __forceinline__ acc mma(double a, double b, acc c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
   }
@@ -509,6 +511,8 @@ __global__ void __launch_bounds__(4 * LX) k_prop_res(ResArgs<T> P) {
   using A4 = typename M::acc;
   constexpr int KX = LX / 16, KY = LY / 16;
   constexpr int S = LX + (sizeof(T) == 4 ? 4 : 2);  // row stride: 16 rows' 16-byte reads on distinct banks
+  using X4 = typename M::lds4;
+  static_assert(alignof(X4) == 16 && S * sizeof(T) % alignof(X4) == 0, "rows start at multiples of the reads' alignment");
   __shared__ __attribute__((aligned(16))) T buf[2][LY * S];
   __shared__ double red[16 * 4];
   __shared__ double mean_s[2];
@@ -590,7 +594,7 @@ __global__ void __launch_bounds__(4 * LX) k_prop_res(ResArgs<T> P) {
     for (int k = 0; k < KX; ++k) {
       A4 a[KY];
 #pragma unroll
-      for (int m = 0; m < KY; ++m) a[m] = *reinterpret_cast<const A4*>(b + (16 * m + n) * S + 16 * k + 4 * g);
+      for (int m = 0; m < KY; ++m) a[m] = *reinterpret_cast<const X4*>(b + (16 * m + n) * S + 16 * k + 4 * g);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll

@@ -800,8 +800,9 @@ __device__ __forceinline__ u32x4 load_chunk(const __bf16* __restrict__ base, int
 }
 
 // 64 -> 64 channels, dilation D.  Twelve waves (three per SIMD): wave t < 9 owns
-// tap t, wave 9 the bias (A = ones), the last two only help staging.  The next tile's chunks are loaded into registers while the
-// current one's MFMAs run, so a tile costs the larger of the two, not their sum.
+// tap t, wave 9 the bias (A = ones), the last two only help staging.  The next
+// tile's chunks are loaded into registers while the current one's MFMAs run, so a
+// tile costs the larger of the two, not their sum.
 constexpr int kWgradThreads = 768;
 template <int D>
 __global__ void __launch_bounds__(kWgradThreads) k_wgrad64(WgradArgs P) {
