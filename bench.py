@@ -131,6 +131,20 @@ def step_bytes_per_site(kind, N, P):
     }.get(kind)
 
 
+def resident(p):
+    """Whether the chain propagators of a grid run in one launch (prop_resident), not
+    in passes: the library's rule, its matrix cycles per contour step."""
+    kx, ky = p["nx"] // 16, p["ny"] // 16
+    cycles = (ky * kx + ky * ky) * 4 * (64 if p["precision"] == 0 else 32) * (-(-kx // 4) if kx > 4 else 1)
+    return p.get("density_mode", 0) != 1 and cycles <= 5120
+
+
+def family_sites(kind, plist):
+    """Sites that a kernel family's launches of one step cover, over the replicas."""
+    passes = kind in ("prop_row", "prop_col")
+    return sum(q["nx"] * q["ny"] for q in plist if not (passes and resident(q)))
+
+
 def window_start(run_len, steps, warmup, every=FALLBACK_EVERY):
     """First step of the timed window: a multiple of `every` (an exact step),
     at least `warmup` steps into the run, as late as a run of `run_len` steps
@@ -333,9 +347,11 @@ def plain_line(args, workload, steps, warmup):
     prof, ksum = kernel_profile(sim, prof_steps, per_step)
     d = sim.diag() if workload != "cfg4" else sim.diag(0)
     sim.close()
+    if workload != "cfg4":
+        plist = [p]
     fams = [k for k in prof if step_bytes_per_site(k, N, P) is not None]
     fam = max(fams, key=lambda k: prof[k]["total_ms"])
-    alg = step_bytes_per_site(fam, N, P) * n * prof_steps / prof[fam]["launches"]
+    alg = step_bytes_per_site(fam, N, P) * family_sites(fam, plist) * prof_steps / prof[fam]["launches"]
     achieved = alg / (prof[fam]["avg_ms"] / 1e3) / 1e9
     roofline = dict(bound="hbm", kernel=fam, achieved=round(achieved, 1), peak=HBM_PEAK_GBS, unit="GB/s",
                     frac=round(achieved / HBM_PEAK_GBS, 4), traffic=measured_traffic(workload, fam),
@@ -343,8 +359,8 @@ def plain_line(args, workload, steps, warmup):
                     launches_per_step=prof[fam]["launches"] / prof_steps, alg_bytes_per_launch=int(alg),
                     kernel_sum_us_per_step=round(ksum, 2))
     breakdown = {k: dict(launches_per_step=v["launches"] / prof_steps, avg_us=round(v["avg_ms"] * 1e3, 3),
-                         gbs=(round(step_bytes_per_site(k, N, P) * n * prof_steps / (v["total_ms"] / 1e3) / 1e9, 1)
-                              if step_bytes_per_site(k, N, P) else None))
+                         gbs=(round(step_bytes_per_site(k, N, P) * family_sites(k, plist) * prof_steps
+                                    / (v["total_ms"] / 1e3) / 1e9, 1) if step_bytes_per_site(k, N, P) else None))
                  for k, v in sorted(prof.items(), key=lambda kv: -kv[1]["total_ms"])}
     return dict(metric=METRIC, value=n * steps / (ms / 1e3), unit="site-updates/s", n_gpus=1, steps=steps,
                 warmup=warmup, ms_per_step=ms / steps, higher_is_better=True, scaling="weak",
