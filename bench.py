@@ -71,13 +71,13 @@ _PROP_FILES = ("fft.hpp", "kernels.hpp")
 _NN_FILES = ("kernels.hpp", "nn.hpp")
 MEASURED_TRAFFIC = {
     # profiles/prop_cfg3_traffic.md: the propagator passes on 1024 x 512, N = 64
-    ("cfg3", "prop_row"): dict(bytes_per_launch=16135474, files=_PROP_FILES,
-                               source_sha256="08bfc791d877eb1afbd7face5f329e76cf03ac61a63cc85f97a62aeb64baf22d"),
-    ("cfg3", "prop_col"): dict(bytes_per_launch=17106137, files=_PROP_FILES,
-                               source_sha256="08bfc791d877eb1afbd7face5f329e76cf03ac61a63cc85f97a62aeb64baf22d"),
+    ("cfg3", "prop_row"): dict(bytes_per_launch=16144431, files=_PROP_FILES,
+                               source_sha256="60d54f4ee7bb9d2b2c256004b2a1effc2d869bdde1ba75eac4927ddd69ae41ec"),
+    ("cfg3", "prop_col"): dict(bytes_per_launch=17092766, files=_PROP_FILES,
+                               source_sha256="60d54f4ee7bb9d2b2c256004b2a1effc2d869bdde1ba75eac4927ddd69ae41ec"),
     # profiles/nn_conv_cfg5q_traffic.md: mean over the two 64 -> 64 launches of a surrogate step
-    ("cfg5q", "nn_conv"): dict(bytes_per_launch=63860115, files=_NN_FILES,
-                               source_sha256="c8445d6bebc2e05a33c74b1f458fde418ced39a43cc11ddbbd4af27128355c1f"),
+    ("cfg5q", "nn_conv"): dict(bytes_per_launch=64041077, files=_NN_FILES,
+                               source_sha256="30d63e782fe100ff40ce811c9346061601fbad3059613a7c112287916f3a0aa9"),
     # profiles/epd3_densities_256_traffic.md: mean over the passes of an evaluation
     ("densities3d_256_N32", "p3_fft"): dict(bytes_per_launch=408023820, files=("epd3.hpp",),
                                             source_sha256="08989653e1ee008741bed3175437b1bfc996838bd5780e9d1dd7840f7c5083fb"),

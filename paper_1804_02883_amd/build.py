@@ -12,7 +12,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libepdlb.so")
 
-SOURCES = ["epdlb.hip"]
+SOURCES = ["epdlb.hip", "prop_plain.hip"]
 HEADERS = ["fft.hpp", "kernels.hpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -22,7 +22,8 @@ FLAGS = [
     "--offload-arch=gfx950",
     # no packed-FP32 VALU forms in device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
+    # a kernel in a header is inline for the linker's sake; the compiler warns that it cannot be inlined
+    "-Wall", "-Wno-unused-function", "-Wno-unused-variable", "-Wno-cuda-compat",
 ]
 
 

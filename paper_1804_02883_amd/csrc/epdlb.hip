@@ -22,6 +22,7 @@
 #include "lb3.hpp"
 #include "lb3_mrt.hpp"
 #include "epd3.hpp"
+#include "prop_launch.hpp"
 
 using namespace epdlb;
 
@@ -225,23 +226,6 @@ const char* const kKindName[K_NUM] = {"field_stats", "advect_update", "finish_st
                                       "nn_conv",     "nn_out",        "nn_norm",       "nn_reset",
                                       "advect_only", "cg_vector",     "force_inv_lb",  "nn_norm_force_row"};
 
-// Profiling: while the profiler has room, the next kernel launch records a
-// start/stop event pair at the kernel's own start and end (AMD's extended
-// launch), so the times are kernel durations even when the host is slower
-// than the GPU.  Recording never blocks.
-thread_local hipEvent_t tl_ev_start = nullptr;
-thread_local hipEvent_t tl_ev_stop = nullptr;
-
-template <typename F, typename... Args>
-void launch_k(F kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s, Args... args) {
-  if (tl_ev_start) {
-    hipExtLaunchKernelGGL(kernel, grid, block, uint32_t(lds), s, tl_ev_start, tl_ev_stop, 0u, args...);
-    tl_ev_start = tl_ev_stop = nullptr;  // one launch per armed pair
-  } else {
-    hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
-  }
-}
-
 struct ProfScope {
   epdlb_ctx* c;
   int kind;
@@ -323,40 +307,14 @@ double lb_nu(const epdlb_params& p) {
   return p.lb_mrt ? (1.0 / 6.0) * (1.0 + p.lb_gamma_s) / (1.0 - p.lb_gamma_s) : (p.lb_tau - 0.5) / 3.0;
 }
 
-int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
-
 // ---------------------------------------------------------------------------
 // Launch helpers (one instantiation per transform length).
 // ---------------------------------------------------------------------------
-template <typename K>
-hipError_t prep_lds(K kernel, size_t bytes) {
-  if (bytes <= 65536) return hipSuccess;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
-}
-
-template <typename T, int L, int R>
-constexpr bool fft_ok() {
-  return (R == 8 || R == 4 || ((R == 16 || R == 2) && sizeof(T) == 4)) && L >= R;
-}
-constexpr int kMaxColThreads = 512;
-// Shapes whose passes come with the plain convolution too (surrogate runs): FP32 at
-// every R, FP64 at the R = 8 that such runs keep.
-template <typename T, int R> constexpr bool plain_ok() { return sizeof(T) == 4 || R == 8; }
-
 template <typename T, int L, int R, bool FIRST>
 hipError_t launch_prop_row_r(const PropArgs<T>& a, hipStream_t s) {
-  if constexpr (fft_ok<T, L, R>()) {
-    using V = LdsView<T, L, R, true, 1>;
-    const size_t lds = 2 * size_t(V::size_elems(a.nf)) * sizeof(T);
-    if (a.plain && !plain_ok<T, R>()) return hipErrorInvalidValue;
-    auto k = a.plain ? k_prop_row<T, L, R, FIRST, !plain_ok<T, R>()> : k_prop_row<T, L, R, FIRST, true>;
-    hipError_t e = prep_lds(k, lds);
-    if (e != hipSuccess) return e;
-    const int tiles = (a.ny / 2 + a.nf - 1) / a.nf;
-    launch_k(k, dim3(tiles, 2, a.nrep), dim3(a.nf * (L / R)), lds, s, a);
-    return hipGetLastError();
-  }
+  if constexpr (fft_ok<T, L, R>())
+    return run_prop_row<T, L, R>(R == 8 && a.plain ? k_prop_row<T, L, R, FIRST, R != 8> : k_prop_row<T, L, R, FIRST, true>,
+                                 a, s);
   return hipErrorInvalidValue;
 }
 template <typename T, int L>
@@ -368,33 +326,22 @@ hipError_t launch_prop_row(const PropArgs<T>& a, int R, hipStream_t s) {
   }
   return launch_prop_row_r<T, L, 8, false>(a, s);
 }
-// The first pass of a propagation.  It comes with R = 4 and 8; in surrogate runs,
-// where every pass rounds as the others do, with every R.
+// The first pass of a propagation.  It comes with R = 4 and 8 (a plain one with
+// every R, so that it rounds as the passes that follow).
 template <typename T, int L>
 hipError_t launch_prop_first(const PropArgs<T>& a, int R, hipStream_t s) {
   PropArgs<T> f = a;
-  const int r = a.plain ? R : (R >= 8 ? 8 : 4);
-  f.nf = clampi(64 * r / L, 1, a.ny / 2);
-  if constexpr (sizeof(T) == 4) {
-    if (r == 16) return launch_prop_row_r<T, L, 16, true>(f, s);
-    if (r == 2) return launch_prop_row_r<T, L, 2, true>(f, s);
-  }
+  const int r = R >= 8 || a.plain ? 8 : 4;
+  f.nf = first_nf(L, r, a.ny);
   return r == 8 ? launch_prop_row_r<T, L, 8, true>(f, s) : launch_prop_row_r<T, L, 4, true>(f, s);
 }
 
 template <typename T, int L, int R, int NF>
 hipError_t launch_prop_col_rn(const PropArgs<T>& a, hipStream_t s) {
-  if constexpr (fft_ok<T, L, R>() && NF * (L / R) <= kMaxColThreads && (sizeof(T) == 4 || NF == 4)) {
-    const size_t elems = col_mapped<L, R>() ? NF * ColView<T, L, R>::kLen : LdsView<T, L, R, false, NF>::size_elems(NF);
-    const size_t lds = elems * sizeof(T2<T>);
-    if (a.plain && !plain_ok<T, R>()) return hipErrorInvalidValue;
-    auto k = a.plain ? k_prop_col<T, L, R, NF, !plain_ok<T, R>()> : k_prop_col<T, L, R, NF, true>;
-    hipError_t e = prep_lds(k, lds);
-    if (e != hipSuccess) return e;
-    const int tiles = (a.nx / 2 + NF - 1) / NF;
-    launch_k(k, dim3(tiles, 2, a.nrep), dim3(NF * (L / R)), lds, s, a);
-    return hipGetLastError();
-  }
+  if constexpr (col_ok<T, L, R, NF>())
+    // (at R = 8, where both forms are, neither remaps)
+    return run_prop_col<T, L, R, NF, col_remap<L, R, true>()>(
+        R == 8 && a.plain ? k_prop_col<T, L, R, NF, R != 8> : k_prop_col<T, L, R, NF, true>, a, s);
   return hipErrorInvalidValue;
 }
 template <typename T, int L, int R>
@@ -553,12 +500,15 @@ hipError_t launch_norm_force_row(const ForceArgs<T>& a, const nn::NormArgs<T>& q
   return hipErrorInvalidValue;
 
 template <typename T> hipError_t prop_row(int L, int R, const PropArgs<T>& a, hipStream_t s) {
+  if (plain_elsewhere(a.plain, R)) return plain_prop_row(L, R, a, false, s);
   EPDLB_SWITCH_L(L, launch_prop_row, T, a, R, s)
 }
 template <typename T> hipError_t prop_first(int L, int R, const PropArgs<T>& a, hipStream_t s) {
+  if (plain_elsewhere(a.plain, R)) return plain_prop_row(L, R, a, true, s);
   EPDLB_SWITCH_L(L, launch_prop_first, T, a, R, s)
 }
 template <typename T> hipError_t prop_col(int L, int R, const PropArgs<T>& a, hipStream_t s) {
+  if (plain_elsewhere(a.plain, R)) return plain_prop_col(L, R, a, s);
   EPDLB_SWITCH_L(L, launch_prop_col, T, a, R, s)
 }
 template <typename T> hipError_t force_row_fwd(int L, int R, const ForceArgs<T>& a, hipStream_t s) {
@@ -1247,7 +1197,7 @@ hipError_t launch_family(epdlb_ctx* c, int fam, int R, int nf, hipStream_t s) {
 // candidate cannot be launched.
 double time_candidate(epdlb_ctx* c, int fam, int R, int nf, int reps) {
   // FP64 surrogate runs keep R = 8 in every pass (see default_shapes)
-  if (c->p.density_mode == 1 && c->p.precision == 0 && R != 8) return -1.0;
+  if (c->p.density_mode == 1 && c->p.precision == 0 && R == 4) return -1.0;
   auto launch = [&](hipStream_t s) {
     return c->p.precision == 0 ? launch_family<double>(c, fam, R, nf, s)
                                : launch_family<float>(c, fam, R, nf, s);

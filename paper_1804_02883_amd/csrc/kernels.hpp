@@ -123,7 +123,7 @@ __device__ __forceinline__ void finish_stats(double* scal, const double (&acc)[4
 
 // Finishes the field statistics: partials of (sum w_A, sum w_B, sum w_S,
 // sum exp(-(w_S - gauge))) -> means, Q_S and the gauge it used.  One block.
-__global__ void __launch_bounds__(256) k_finish_stats(const double* partials, int nslots, double* scal,
+inline __global__ void __launch_bounds__(256) k_finish_stats(const double* partials, int nslots, double* scal,
                                                       long n, double dA, long rs) {
   __shared__ double red[16 * 4];
   partials = sh(partials, long(blockIdx.z) * rs);
@@ -223,6 +223,11 @@ __device__ __forceinline__ void convolve(T* re, T* im, int j, const V& lds, cons
   fft_inverse<T, L, R>(re, im, j, lds, twi);
   if constexpr (BASE) add_const<R>(re, im, T(1));
 }
+
+// Whether a column pass changes its lane mapping (see ColMap).  The plain passes
+// keep one mapping, in which the compiler contracts products and sums as it did
+// when their bits were set.
+template <int L, int R, bool BASE> constexpr bool col_remap() { return BASE && col_mapped<L, R>(); }
 
 // The same over the columns of a block (ColMap); g in the wave mapping.
 template <typename T, int L, int R, bool BASE>
@@ -367,7 +372,7 @@ __global__ void __launch_bounds__(512) k_prop_col(PropArgs<T> P) {
   __shared__ double red[16 * 1];
   const int f = threadIdx.x % NF, j = threadIdx.x / NF;
   V lds{reinterpret_cast<T2<T>*>(smem_raw), f};
-  constexpr bool kMap = col_mapped<L, R>();
+  constexpr bool kMap = col_remap<L, R, BASE>();
   const int jw = kMap ? int(threadIdx.x) % TL : j;  // the lane within the transform between the exchanges
   P.shift(long(blockIdx.z) * P.rs);
   const int lt = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
