@@ -79,8 +79,8 @@ MEASURED_TRAFFIC = {
     ("cfg5q", "nn_conv"): dict(bytes_per_launch=64041077, files=_NN_FILES,
                                source_sha256="30d63e782fe100ff40ce811c9346061601fbad3059613a7c112287916f3a0aa9"),
     # profiles/epd3_densities_256_traffic.md: mean over the passes of an evaluation
-    ("densities3d_256_N32", "p3_fft"): dict(bytes_per_launch=408023820, files=("epd3.hpp",),
-                                            source_sha256="08989653e1ee008741bed3175437b1bfc996838bd5780e9d1dd7840f7c5083fb"),
+    ("densities3d_256_N32", "p3_fft"): dict(bytes_per_launch=408024350, files=("epd3.hpp",),
+                                            source_sha256="5b929f067bc05bebf49c75917d871ab8812566e5d3db88fbaf60b8a30d0c3998"),
     # profiles/lb3_fluid3d_256_traffic.md: the step kernel without moment stores
     ("fluid3d_256", "lb3"): dict(bytes_per_launch=2751540306, files=("lb3.hpp",),
                                  source_sha256="00612d3692132a490494ae8af15af4cd91f576f0cf2aeadfdd24c455de263e97"),

@@ -17,8 +17,10 @@
 // pass is 4-5 us).  As one three-dimensional complex transform pair per step, a
 // chain at a time, a step moved 22 planes per chain in 5 launches.  Measured at
 // 256^3 FP32, N = 32: 320 launches of 120 us, 39.4 ms per evaluation, before;
-// 65 launches of 83 us (403 MB each, 4.8 TB/s; a copy reaches 5.05), 6.45 ms,
-// now.  128^3: 4.99 -> 1.07 ms (FP32), 9.32 -> 1.74 ms (FP64).
+// 65 launches of 84-86 us in the mean (events at their own start and end; 403 MB
+// each, 4.7-4.8 TB/s, where a copy reaches 5.05), 6.75-7.04 ms, now, by card (6.45
+// on the best).  Under the kernel trace: 89-90 us along y and z, 104 along x, 132-136
+// the first.  128^3: 4.99 -> 1.07-1.13 ms (FP32), 9.32 -> 1.74 ms (FP64).
 //
 // The sums (gauge, Q_P, Q_S) are FP64 block partials in fixed slots, added in
 // slot order.
@@ -106,7 +108,7 @@ __device__ __forceinline__ void convolve_exact(T* re, T* im, int j, const V& lds
 // nothing), offsets are 32 bits (a plane is at most 2^27 sites).  With the factor
 // chosen by a branch per value, 64 x 32 x 16 FP64 at N = 16 took 0.237 ms, and
 // 0.196 ms now.  FP32 is held to 128 registers, four waves per SIMD: at 256^3 the
-// 129th cost 8.08 against 6.45 ms.
+// 129th cost 8.08 against 6.45 ms on the same card.
 template <typename T, int L, int R, bool CONTIG, int NF, bool FIRST>
 __global__ void __launch_bounds__(512, sizeof(T) == 4 ? 4 : 2) k_p3_pass(PassArgs<T> P) {
   static_assert(CONTIG || !FIRST, "the first pass runs along x");

@@ -1505,11 +1505,13 @@ int get_graph(epdlb_ctx* c, int steps, int kind, hipGraphExec_t* out) {
 // each win until the exchanges cost more: R = 4, except for lengths where R = 8
 // makes a transform one wave (rows of 512) or halves 512-lane barriers (columns
 // of 512 and more).  Rows: one wave per block, two of 512; columns: 4 pairs, which
-// gives twice the blocks of 8 and still 32-byte segments.  Measured per pass
-// (us), R = 8 with 256-lane rows and 8 column pairs -> these: 256 x 256 rows 5.2 ->
-// 3.5, columns 6.2 -> 4.8; 1024 x 512 rows 8.7 -> 7.7, columns 8.8 -> 8.2; 512 x 512
-// rows 5.6 -> 5.2, columns 8.2 -> 6.8; 128 x 128 4.8 -> 3.4 and 5.1 -> 4.0; FP64
-// 256 x 128 8.1 -> 4.0 and 5.1 -> 4.5.
+// gives twice the blocks of 8 and still 32-byte segments.  Measured per pass (us),
+// launches of one pass back to back in a graph, R = 8 with 256-lane rows and 8 column
+// pairs -> these: 256 x 256 rows 5.2 -> 3.5, columns 6.2 -> 4.8; 1024 x 512 rows 9.3 ->
+// 8.4, columns 9.35 -> 8.8; 512 x 512 rows 6.0 -> 5.6, columns 8.6 -> 7.3; 128 x 128
+// 4.8 -> 3.4 and 5.1 -> 4.0; FP64 256 x 128 8.1 -> 4.0 and 5.1 -> 4.5.  In a step, where
+// rows and columns alternate, the same passes take 8.8-9.3 and 9.2-9.9 us at 1024 x
+// 512, 5.5-6.5 and 7.2-8.2 at 512 x 512, by card.
 // A surrogate context starts at R = 8, and its passes take the plain convolution at
 // every R: its network reads the potentials rounded to BF16, so where a transform
 // rounds differently whole BF16 steps move (2.6e-5 of the potentials after 50 steps
@@ -2615,7 +2617,7 @@ void epdlb_destroy(epdlb_ctx* c) {
   if (c->cg_host) (void)hipHostFree(c->cg_host);
   if (c->snap) (void)hipHostFree(c->snap);
   if (c->snap_ev) (void)hipEventDestroy(c->snap_ev);
-    if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
+  if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
   delete c;
 }
 
@@ -3498,7 +3500,7 @@ void epdlb_lb3_destroy(epdlb_lb3* c) {
   if (!c) return;
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
-    if (c->mem) (void)hipFree(c->mem);
+  if (c->mem) (void)hipFree(c->mem);
   if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
   delete c;
 }
@@ -3558,8 +3560,8 @@ int p3_launch(const epd3::PassArgs<T>& a, hipStream_t s, int nf, long blocks) {
 // blocks per chain).  Blocks are wide where both chains together still give two per
 // CU, else one wave, so that a small grid reaches more CUs.  An evaluation with
 // wide / narrow blocks: 64 x 32 x 16 FP64, N = 16: 0.196 / 0.155 ms; 64^3 FP32,
-// N = 32: 0.368 / 0.338; 128^3: 1.07 / 1.23 (FP64 1.74 / 1.86); 256^3: 6.45 / 8.02
-// (wide blocks read whole cache lines along y and z).
+// N = 32: 0.368 / 0.338; 128^3: 1.07 / 1.23 (FP64 1.74 / 1.86); 256^3: 6.45 / 8.02, each
+// pair on one card (wide blocks read whole cache lines along y and z).
 template <typename T, int L, bool CONTIG>
 int p3_pass_shape(const epd3::PassArgs<T>* a, bool first, hipStream_t s, long units, long* blocks) {
   constexpr int R = epd3::values_per_lane<L>(), tl = L / R;
@@ -3940,7 +3942,7 @@ void epdlb_epd3_destroy(epdlb_epd3* c) {
   if (!c) return;
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
-    if (c->mem) (void)hipFree(c->mem);
+  if (c->mem) (void)hipFree(c->mem);
   if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
   delete c;
 }

@@ -3,15 +3,18 @@
 //
 // One host thread that converts into a fresh vector, a copy from or to pageable
 // memory, and a result array whose pages are touched for the first time bound
-// these calls: reading rho and u of a 192^3 FP32 fluid (28 M values) took
-// 43 ms, the densities of a 256^3 grid (50 M values each way) 115 ms beside
-// their kernels, at 57 GB/s of PCIe a few milliseconds' worth.  Here the copies
-// go through a ring of pinned slots while several threads convert the other
-// slots, so conversion, first touch and copy overlap: HOSTIO_FIGURES
+// these calls, at 57 GB/s of PCIe a few milliseconds' worth.  From kStageMin values
+// on the copies go through a ring of pinned slots while several threads convert the
+// other slots, so conversion, first touch and copy overlap.  Measured, before ->
+// now: 7.1 M and 21.2 M values of a 192^3 FP32 fluid read 57 -> 25.6 ms (21.8 of
+// them for the first array, whose pages fault one by one), 21.2 M set 30 -> 8.4 ms;
+// 2.1 M values on a context of their own, the ring's making included, 3.4 -> 2.1 ms
+// up and 3.1 -> 1.8 ms down; 1.2 M 1.9 -> 1.7 and 1.8 -> 1.5, so the line lies at 2^20.
 //
-// A stage belongs to one context: allocated at its first large transfer, given
-// back with it.  Threads live for one call.  Smaller transfers (kStageMin) keep
-// the plain path, whose cost is below that of starting the threads.
+// The rings belong to the process: a transfer leases one of its device's, and the
+// idle ones go when the last context does.  Making one takes 0.13-0.4 ms.  Threads
+// live for one call.  Smaller transfers keep the plain path, whose cost is below
+// that of starting the threads (0.11 ms).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <sched.h>
