@@ -1246,10 +1246,12 @@ void drop_graphs(epdlb_ctx* c) {
   c->graphs.clear();
 }
 
+// FP64 surrogate runs have lines of their own ("x1s"): theirs are R = 8 throughout,
+// and in a shared line an exact run would take over that shape, or they an R = 4.
 std::string tune_key(const epdlb_ctx* c, int fam) {
   char buf[128];
-  std::snprintf(buf, sizeof(buf), "gfx950 %d %d %d %d x%d %s", c->p.nx, c->p.ny, c->p.n_contour,
-                c->p.precision, c->nrep, kFamilyName[fam]);
+  std::snprintf(buf, sizeof(buf), "gfx950 %d %d %d %d x%d%s %s", c->p.nx, c->p.ny, c->p.n_contour, c->p.precision,
+                c->nrep, c->p.density_mode == 1 && c->p.precision == 0 ? "s" : "", kFamilyName[fam]);
   return buf;
 }
 

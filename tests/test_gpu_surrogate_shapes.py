@@ -46,6 +46,23 @@ def test_lines_of_equal_values_pass_unchanged(family, shapes):
     sim.close()
 
 
+def test_fp64_tune_lines_are_their_own(tmp_path):
+    from paper_1804_02883_amd import Simulation
+    cache = tmp_path / "tune.txt"
+    families = ("prop_row", "prop_col", "force_row", "force_col")
+    lines = "".join(f"gfx950 {NX} {NY} 6 0 x1 {f} 4 4 1.000\n" for f in families)
+    cache.write_text(lines)
+    sim = _sim(0)
+    sim.autotune(2, str(cache))
+    assert all(R == 8 for R, _ in sim.shapes().values())
+    sim.close()
+    sim = Simulation(preset("cfg1", nx=NX, ny=NY, n_contour=6, f_A=0.4, precision=0))
+    sim.autotune(2, str(cache))
+    assert sim.shapes() == {f: (4, 4) for f in families}
+    sim.close()
+    assert cache.read_text().startswith(lines) and cache.read_text().count(" x1s ") == 4
+
+
 def test_fp64_stays_at_eight():
     from paper_1804_02883_amd import EpdlbError
     sim = _sim(0)
